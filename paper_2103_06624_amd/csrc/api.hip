@@ -2568,7 +2568,8 @@ void joint_reverse(cv_bound* h, hipStream_t s) {
     JointLayer& q = J->lay[t];
     cv_bound* x = q.h;
     launch_joint_weights(q.w, J->dL, J->dU, J->ml, J->mu, B, q.d, q.off, nd, s);
-    launch_joint_reduce(q.gash, q.garow, q.gbsh, q.gbrow, q.w, x->bt, B, q.d, q.nnz, s);
+    const int ucmax = *std::max_element(x->h_ucount.begin(), x->h_ucount.end());
+    launch_joint_reduce(q.gash, q.garow, q.gbsh, q.gbrow, q.w, x->bt, B, q.d, ucmax, x->d_split_dom, q.nnz, s);
     launch_joint_cot(J->dL, J->dU, x->bt.status, x->acomp, x->zchord, q.w, J->lcur, J->ucur, x->bt, col0, x->nd, nd,
                      B, s);
   }

@@ -310,8 +310,9 @@ void launch_joint_clip(const float* lb, int d, int off, const float* lroot, cons
 void launch_joint_bcast(float* arow, const float* ash, float* brow, const float* bsh, const Batch& bt, int d,
                         int64_t nnz, hipStream_t s);
 // shared gradients = per side, sum over its rows of w[row] x the row's gradient
+// (ucmax: the largest unstable count of any subdomain)
 void launch_joint_reduce(float* gash, const float* garow, float* gbsh, const float* gbrow, const float* w,
-                         const Batch& bt, int B, int d, int64_t nnz, hipStream_t s);
+                         const Batch& bt, int B, int d, int ucmax, const int* split_dom, int64_t nnz, hipStream_t s);
 // dL, dU [B][nd] += d(sum_rows w g)/dl, /du at the unstable neurons of columns
 // [col0, nd_x) of a handle (w null: every row weighs 1), from its stored A
 // (acomp) and the adjoint's zbar at upper-chord neurons (zchord)
