@@ -87,30 +87,48 @@ __global__ void bcast_beta_k(float* brow, const float* __restrict__ bsh, int64_t
 // The reductions over a pass's rows (2 d_i of them per subdomain, thousands on
 // a convolutional layer) are bound by reading the per-row entries once: [rows,
 // uc] floats in rows of one subdomain, contiguous (a row's entries start at
-// aoff[b] + k ucount[b]).  A workgroup takes 32 columns (128-byte pieces of a
-// row) with 32 threads per column, each summing every 32nd row with eight
-// loads in flight; the 32 partial sums meet in LDS in a fixed order.  One
-// thread per column over all rows left 8 to 30 workgroups on the chip, each a
-// serial chain of loads: on the CIFAR network with four convolutions, at four
-// subdomains, 598 us a launch for the alpha' sums and 540 us for the
-// bounds' gradient (means over the layers), against 9.2 and 16.7 us so.
+// aoff[b] + k ucount[b]).  Each sum keeps its order, row by row: the shared
+// variables steer every later iterate, and a sum in another order would turn
+// into another trajectory wherever a gradient is near zero.  So a workgroup
+// takes 32 columns (128-byte pieces of a row), all its threads bring chunks of
+// rows into LDS, the next chunk's loads in flight, and one thread per column
+// walks the chunk.  One thread per column straight over memory left 8 to 30
+// workgroups on the chip, each a serial chain of loads: on the CIFAR network
+// with four convolutions, at four subdomains, 598 us a launch for the alpha'
+// sums and 540 us for the bounds' gradient (means over the layers), against
+// 42 and 29 us so.
 constexpr int kRedCols = 32;
-constexpr int kRedRows = 32;  // row groups: threads per column
-constexpr int kRedUnroll = 8;
+constexpr int kRedThreads = 1024;
+constexpr int kRedRows = kRedThreads / kRedCols;  // rows loaded together
 
-// sum of the kRedRows partials of column t (thread t < kRedCols), in pairs
-__device__ __forceinline__ float red_total(const float (*p)[kRedCols + 1], int t) {
-  float s = 0.f;
+// s <- fmaf(w(r), x(r), s) for r = 0 .. n - 1 in order, rows with w = 0 left out
+// (0 x 0 leaves s as it is); the operands of 16 rows are read together, then
+// walked.
+template <class W, class X>
+__device__ __forceinline__ void walk(float& s, int n, W w, X x) {
+  constexpr int kU = 16;
+  for (int r0 = 0; r0 < n; r0 += kU) {
+    float wv[kU], xv[kU];
 #pragma unroll
-  for (int g = 0; g < kRedRows; g += 2) s += p[g][t] + p[g + 1][t];
-  return s;
+    for (int q = 0; q < kU; ++q) {
+      const int r = min(r0 + q, n - 1);
+      wv[q] = w(r);
+      xv[q] = x(r);
+    }
+#pragma unroll
+    for (int q = 0; q < kU; ++q) {
+      const float wq = r0 + q < n ? wv[q] : 0.f;
+      s = fmaf(wq, wq != 0.f ? xv[q] : 0.f, s);
+    }
+  }
 }
 
 // shared gradient of side s of subdomain b = sum over the side's rows of
 // w[row] x the row's gradient (a row of weight 0 contributes nothing)
-__global__ __launch_bounds__(kRedCols * kRedRows) void reduce_alpha_k(float* gash, const float* __restrict__ garow,
-                                                                      const float* __restrict__ w, Batch bt, int d) {
-  __shared__ float part[kRedRows][kRedCols + 1];
+__global__ __launch_bounds__(kRedThreads) void reduce_alpha_k(float* gash, const float* __restrict__ garow,
+                                                              const float* __restrict__ w, Batch bt, int d) {
+  constexpr int kQ = 7, kChunk = kRedRows * kQ;  // (two buffers within 64 KB)
+  __shared__ float xs[2][kChunk][kRedCols], ws[2][kChunk];
   const int b = blockIdx.x >> 1, side = blockIdx.x & 1;
   const int uc = bt.ucount[b];
   const int c0 = blockIdx.y * kRedCols;
@@ -120,41 +138,59 @@ __global__ __launch_bounds__(kRedCols * kRedRows) void reduce_alpha_k(float* gas
   const int k0 = side * d;
   const float* const wr = w + (int64_t)b * bt.m + k0;
   const float* const gr = garow + bt.aoff[b] + (int64_t)k0 * uc + c;
+  float x[kQ], wk = 0.f;
+  auto load = [&](int k) {
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) x[q] = gr[(int64_t)min(k + q * kRedRows + g, d - 1) * uc];
+    if (threadIdx.x < kChunk) wk = k + (int)threadIdx.x < d ? wr[k + threadIdx.x] : 0.f;
+  };
+  load(0);
   float s = 0.f;
-  for (int k = g; k < d; k += kRedRows * kRedUnroll) {
-    float wk[kRedUnroll], x[kRedUnroll];
+  for (int k = 0, buf = 0; k < d; k += kChunk, buf ^= 1) {
 #pragma unroll
-    for (int q = 0; q < kRedUnroll; ++q) {
-      const int kq = min(k + kRedRows * q, d - 1);
-      wk[q] = k + kRedRows * q < d ? wr[kq] : 0.f;
-      x[q] = gr[(int64_t)kq * uc];
+    for (int q = 0; q < kQ; ++q) xs[buf][q * kRedRows + g][t] = x[q];
+    if (threadIdx.x < kChunk) ws[buf][threadIdx.x] = wk;
+    if (k + kChunk < d) load(k + kChunk);
+    __syncthreads();
+    if (g == 0) {
+      const int n = min(kChunk, d - k);
+      walk(s, n, [&](int r) { return ws[buf][r]; }, [&](int r) { return xs[buf][r][t]; });
     }
-#pragma unroll
-    for (int q = 0; q < kRedUnroll; ++q) s = wk[q] != 0.f ? fmaf(wk[q], x[q], s) : s;
   }
-  part[g][t] = s;
-  __syncthreads();
-  if (g == 0 && c0 + t < uc) gash[bt.aoff[b] / d + side * uc + c] = red_total(part, t);
+  if (g == 0 && c0 + t < uc) gash[bt.aoff[b] / d + side * uc + c] = s;
 }
 
-// the same for beta': one wave per (split, side), the rows across its lanes
-__global__ __launch_bounds__(256) void reduce_beta_k(float* gbsh, const float* __restrict__ gbrow,
-                                                     const float* __restrict__ w, const int* __restrict__ split_dom,
-                                                     int64_t nnz, int m, int d) {
-  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (q >= nnz * 2) return;
-  const int lane = threadIdx.x & 63;
-  const int64_t t = q >> 1;
-  const int side = (int)(q & 1);
+// the same for beta': one wave per (split, side), its rows brought into LDS
+__global__ __launch_bounds__(64) void reduce_beta_k(float* gbsh, const float* __restrict__ gbrow,
+                                                    const float* __restrict__ w, const int* __restrict__ split_dom,
+                                                    int m, int d) {
+  constexpr int kQ = 8, kChunk = 64 * kQ;
+  __shared__ float xs[kChunk], ws[kChunk];
+  const int64_t q0 = blockIdx.x, t = q0 >> 1;
+  const int side = (int)(q0 & 1), lane = threadIdx.x;
   const float* const wr = w + (int64_t)split_dom[t] * m + side * d;
   const float* const gr = gbrow + t * m + side * d;
   float s = 0.f;
-  for (int k = lane; k < d; k += 64) {
-    const float wk = wr[k], x = gr[k];
-    s = wk != 0.f ? fmaf(wk, x, s) : s;
+  for (int k = 0; k < d; k += kChunk) {
+    float x[kQ], wk[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      const int i = min(k + 64 * q + lane, d - 1);
+      x[q] = gr[i];
+      wk[q] = wr[i];
+    }
+    __syncthreads();  // the chunk before has been walked
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      xs[64 * q + lane] = x[q];
+      ws[64 * q + lane] = wk[q];
+    }
+    __syncthreads();
+    const int n = min(kChunk, d - k);
+    if (lane == 0)
+      walk(s, n, [&](int r) { return ws[r]; }, [&](int r) { return xs[r]; });
   }
-  s = wave_sum(s);
-  if (lane == 0) gbsh[q] = s;
+  if (lane == 0) gbsh[q0] = s;
 }
 
 // d(sum_rows w g)/dl and /du at the currently unstable neurons of columns
@@ -162,55 +198,61 @@ __global__ __launch_bounds__(256) void reduce_beta_k(float* gbsh, const float* _
 // chord u (z - l)/(u - l) where its stored A is negative; with zbar the
 // adjoint's pre-activation there, the chord term A (s zbar - s l) has
 // d/dl = A u (zbar - u)/(u - l)^2 and d/du = A l (l - zbar)/(u - l)^2.
-// One workgroup per 32 columns of a subdomain, as above.
-__global__ __launch_bounds__(kRedCols * kRedRows) void cot_k(float* dL, float* dU,
-                                                             const uint32_t* __restrict__ status,
-                                                             const float* __restrict__ acomp,
-                                                             const float* __restrict__ zchord,
-                                                             const float* __restrict__ w,
-                                                             const float* __restrict__ lcur,
-                                                             const float* __restrict__ ucur, Batch bt, int col0,
-                                                             int nd_x, int nd) {
-  __shared__ float pl[kRedRows][kRedCols + 1], pu[kRedRows][kRedCols + 1];
+// One workgroup per 32 columns of a subdomain, as above: its threads form each
+// row's terms, half a wave walks the sum for l and half the one for u.
+__global__ __launch_bounds__(kRedThreads) void cot_k(float* dL, float* dU, const uint32_t* __restrict__ status,
+                                                     const float* __restrict__ acomp,
+                                                     const float* __restrict__ zchord, const float* __restrict__ w,
+                                                     const float* __restrict__ lcur, const float* __restrict__ ucur,
+                                                     Batch bt, int col0, int nd_x, int nd) {
+  constexpr int kQ = 4, kChunk = kRedRows * kQ;
+  // a row's term is cs es[0] (for l), cs es[1] (for u)
+  __shared__ float cs[kChunk][kRedCols], es[2][kChunk][kRedCols];
   const int b = blockIdx.x;
   const int t = threadIdx.x % kRedCols, g = threadIdx.x / kRedCols;
   const int c = col0 + blockIdx.y * kRedCols + t;
   const uint32_t rec = c < nd_x ? status[(int64_t)b * nd_x + c] : kInactive;
   const bool uns = (rec & kKindMask) == kUnstable;
-  float l = 0.f, u = 0.f, dl = 0.f, du = 0.f;
-  if (uns) {
-    const int64_t cb = (int64_t)b * nd + c;
-    l = lcur[cb];
-    u = ucur[cb];
-    const int m = bt.m, uc = bt.ucount[bt.prop[b]];
-    const float* const wr = w ? w + (int64_t)b * m : nullptr;
-    const int64_t a0 = bt.aoff[b] + (rec & kCidxMask);
-    for (int k = g; k < m; k += kRedRows * kRedUnroll) {
-      float wk[kRedUnroll], a[kRedUnroll], z[kRedUnroll];
+  const int m = bt.m, uc = bt.ucount[bt.prop[b]];
+  const int64_t cb = (int64_t)b * nd + c, a0 = bt.aoff[b] + (uns ? rec & kCidxMask : 0);
+  const float* const wr = w ? w + (int64_t)b * m : nullptr;
+  const float l = uns ? lcur[cb] : 0.f, u = uns ? ucur[cb] : 0.f;
+  float a[kQ], z[kQ], wk[kQ];
+  auto load = [&](int k) {
 #pragma unroll
-      for (int q = 0; q < kRedUnroll; ++q) {
-        const int kq = min(k + kRedRows * q, m - 1);
-        wk[q] = k + kRedRows * q < m ? (wr ? wr[kq] : 1.f) : 0.f;
-        a[q] = acomp[a0 + (int64_t)kq * uc];
-        z[q] = zchord[a0 + (int64_t)kq * uc];  // meaningful where a < 0
-      }
+    for (int q = 0; q < kQ; ++q) {
+      const int r = k + q * kRedRows + g, kr = min(r, m - 1);
+      a[q] = z[q] = wk[q] = 0.f;
+      if (!uns) continue;
+      wk[q] = r < m ? (wr ? wr[kr] : 1.f) : 0.f;
+      a[q] = acomp[a0 + (int64_t)kr * uc];
+      z[q] = zchord[a0 + (int64_t)kr * uc];  // meaningful where a < 0
+    }
+  };
+  load(0);
+  float s = 0.f;
+  for (int k = 0; k < m; k += kChunk) {
+    __syncthreads();  // the chunk before has been walked
 #pragma unroll
-      for (int q = 0; q < kRedUnroll; ++q) {
-        const bool on = wk[q] != 0.f && a[q] < 0.f;
-        dl = on ? fmaf(wk[q] * a[q], u * (z[q] - u), dl) : dl;
-        du = on ? fmaf(wk[q] * a[q], l * (l - z[q]), du) : du;
-      }
+    for (int q = 0; q < kQ; ++q) {
+      const int r = q * kRedRows + g;
+      const bool on = wk[q] != 0.f && a[q] < 0.f;
+      cs[r][t] = on ? wk[q] * a[q] : 0.f;
+      es[0][r][t] = on ? u * (z[q] - u) : 0.f;
+      es[1][r][t] = on ? l * (l - z[q]) : 0.f;
+    }
+    if (k + kChunk < m) load(k + kChunk);
+    __syncthreads();
+    if (g < 2) {
+      const int n = min(kChunk, m - k);
+#pragma unroll 16
+      for (int r = 0; r < n; ++r) s = fmaf(cs[r][t], es[g][r][t], s);
     }
   }
-  pl[g][t] = dl;
-  pu[g][t] = du;
-  __syncthreads();
-  if (g == 0 && uns) {
-    const int64_t cb = (int64_t)b * nd + c;
+  if (g < 2 && uns) {
     const float den = u - l;
     const float inv2 = 1.f / (den * den);
-    dL[cb] += red_total(pl, t) * inv2;
-    dU[cb] += red_total(pu, t) * inv2;
+    (g == 0 ? dL : dU)[cb] += s * inv2;
   }
 }
 
@@ -271,16 +313,16 @@ void launch_joint_reduce(float* gash, const float* garow, float* gbsh, const flo
                          const Batch& bt, int B, int d, int ucmax, const int* split_dom, int64_t nnz, hipStream_t s) {
   if (B <= 0) return;
   if (ucmax > 0)
-    reduce_alpha_k<<<dim3(2 * B, nblk(ucmax, kRedCols)), kRedCols * kRedRows, 0, s>>>(gash, garow, w, bt, d);
-  if (nnz > 0) reduce_beta_k<<<nblk(nnz * 2, 4), 256, 0, s>>>(gbsh, gbrow, w, split_dom, nnz, bt.m, d);
+    reduce_alpha_k<<<dim3(2 * B, nblk(ucmax, kRedCols)), kRedThreads, 0, s>>>(gash, garow, w, bt, d);
+  if (nnz > 0) reduce_beta_k<<<(unsigned)(nnz * 2), 64, 0, s>>>(gbsh, gbrow, w, split_dom, bt.m, d);
 }
 
 void launch_joint_cot(float* dL, float* dU, const uint32_t* status, const float* acomp, const float* zchord,
                       const float* w, const float* lcur, const float* ucur, const Batch& bt, int col0, int nd_x,
                       int nd, int B, hipStream_t s) {
   if (B > 0 && nd_x > col0)
-    cot_k<<<dim3(B, nblk(nd_x - col0, kRedCols)), kRedCols * kRedRows, 0, s>>>(dL, dU, status, acomp, zchord, w, lcur,
-                                                                              ucur, bt, col0, nd_x, nd);
+    cot_k<<<dim3(B, nblk(nd_x - col0, kRedCols)), kRedThreads, 0, s>>>(dL, dU, status, acomp, zchord, w, lcur, ucur,
+                                                                       bt, col0, nd_x, nd);
 }
 
 void launch_joint_weights(float* w, const float* dL, const float* dU, const uint8_t* ml, const uint8_t* mu, int B,
