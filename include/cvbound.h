@@ -340,7 +340,8 @@ int cv_bound_set_tiling(cv_bound *h, int32_t tiling);
  *   1  row-major, the weights read from global memory (L1/L2);
  *   2  subdomain-major: each workgroup takes the specification rows of one
  *      subdomain in turn and keeps the subdomain's status records and its
- *      property's chords (or box) in registers across them, weights in LDS;
+ *      property's chords (or box) in registers across them, weights in LDS
+ *      (on most layers with the epilogue on the matrix cores' own tile);
  *   3  subdomain-major, weights from global memory.
  * cv_bound_num_conv_variants: how many there are.
  * cv_bound_set_conv_variant: force `variant` on every conv layer of h (and of

@@ -315,6 +315,12 @@ int conv_mode(int layer_index, bool bwd, bool first_dense) {
   return bwd ? (layer_index == 0 ? kBwdConc : kBwdRelax) : (layer_index == 0 ? kFwdX : kFwd);
 }
 
+// The concretisation and the adjoint's step of a conv first layer share the
+// order of the sign planes: both by register tiles, or neither.
+void couple_first(DevLayer& d) {
+  if (!d.bwd.reg.on || !d.fwd.reg.on) d.bwd.reg.on = d.fwd.reg.on = 0;
+}
+
 // Kernel variant of every conv layer in both directions: `forced` >= 0 forces
 // that variant where it can run (elsewhere the default), -1 takes the tuned
 // choice for each layer shape, else the default plan.
@@ -325,6 +331,7 @@ void assign_conv_variants(cv_bound* h, int forced) {
     for (int dir = 0; dir < 2; ++dir) {
       ConvPlan& pl = dir == 0 ? d.bwd : d.fwd;
       pl = dir == 0 ? d.bwd_def : d.fwd_def;
+
       const int mode = conv_mode(i, dir == 0, false);
       int v = forced;
       if (v < 0) {
@@ -334,6 +341,7 @@ void assign_conv_variants(cv_bound* h, int forced) {
       }
       if (v >= 0) (void)conv_plan_variant(mode, pl, v);
     }
+    if (i == 0) couple_first(d);
   }
 }
 
@@ -635,6 +643,73 @@ void plan_conv(const cv_layer& ly, HostPlan& o) {
   plan_border(o);
 }
 
+// The register-tile kernel's tables of a built plan (ConvReg): its columns
+// reordered, the weights four K steps together.  col(t, g, r): the plan's
+// column there, or -1.  Empty tables where the layer has no such order.
+struct HostReg {
+  std::vector<int4> ob;
+  std::vector<float4> w4;
+  std::vector<int2> xt;
+  ConvReg r{};
+};
+
+void plan_reg(const cv_layer& ly, bool bwd, const HostPlan& o, HostReg& q) {
+  const ConvPlan& p = o.p;
+  const int C = bwd ? ly.in_c : ly.out_c, s = ly.stride;
+  const bool poly = bwd && s == 2, pair = C <= 8 && (!bwd || s == 1);
+  if (bwd && s > 2) return;
+  ConvReg& r = q.r;
+  r.plane = p.oh * p.ow;
+  r.ts = poly ? 4 : 16;
+  const int tiles = poly ? (C + 3) / 4 : pair ? 1 : (C + 15) / 16;
+  r.nt = tiles <= 1 ? 1 : tiles <= 2 ? 2 : tiles <= 4 ? 4 : 8;
+  if (tiles > 8) return;
+  r.n_mt = p.mpad / 16;
+  r.ksp = 1;
+  auto column = [&](int t, int g, int rr) -> int {
+    if (poly) return 4 * t + rr < C ? g * C + 4 * t + rr : -1;
+    if (!pair) return 16 * t + 4 * g + rr < C ? 16 * t + 4 * g + rr : -1;
+    for (int n = 0; n < 2 * C; ++n) {
+      int px, ch;
+      pair_col(n, C, px, ch);
+      if (px == (g & 1) && ch == rr + 4 * (g >> 1)) return n;
+    }
+    return -1;
+  };
+  int cols[8 * 16];
+  r.rc = 0;
+  for (int t = 0; t < r.nt; ++t)
+    for (int g = 0; g < 4; ++g)
+      for (int rr = 0; rr < 4; ++rr) {
+        const int n = cols[t * 16 + g * 4 + rr] = column(t, g, rr);
+        if (n >= 0) r.rc = std::max(r.rc, rr + 1);
+      }
+  auto col = [&](int t, int g, int rr) { return cols[t * 16 + g * 4 + rr]; };
+  r.rc = r.rc <= 3 ? 3 : 4;  // (the kernel's instances)
+  r.nwords = r.n_mt * r.nt * r.rc;
+  q.ob.resize((size_t)r.n_mt * 64);
+  for (int m = 0; m < r.n_mt * 16; ++m)
+    for (int g = 0; g < 4; ++g) {
+      const int4 mo = o.mt[m];
+      int at = -1;
+      const int n = col(0, g, 0);
+      if (n >= 0 && m < o.M) {
+        const int4 ne = o.nt[n];
+        const int y = p.osy * mo.z + ne.x, x = p.osx * mo.w + ne.y;
+        if (y >= 0 && y < p.oh && x >= 0 && x < p.ow) at = ne.z + y * p.ow + x;
+      }
+      q.ob[(size_t)(m / 16) * 64 + g * 16 + m % 16] = make_int4(mo.x, at, 0, 0);
+    }
+  auto wv = [&](int k, int n) { return n < 0 ? 0.f : o.wm[((size_t)(k / 4) * p.nt + n / 16) * 64 + (k % 4) * 16 + n % 16]; };
+  q.w4.resize((size_t)(p.kpad / 16) * r.nt * 64);
+  for (int ps = 0; ps < p.kpad / 16; ++ps)
+    for (int t = 0; t < r.nt; ++t)
+      for (int l = 0; l < 64; ++l) {
+        const int n = col(t, (l % 16) / 4, l % 4), k = ps * 16 + l / 16;
+        q.w4[((size_t)ps * r.nt + t) * 64 + l] = make_float4(wv(k, n), wv(k + 4, n), wv(k + 8, n), wv(k + 12, n));
+      }
+}
+
 // Weight placement and LDS bytes of a built plan.
 void plan_finish(ConvPlan& p) {
   // a weight matrix over 16 KB stays in global memory (more workgroups fit per CU)
@@ -693,27 +768,66 @@ bool finite_all(const float* p, int64_t n) {
   return true;
 }
 
-int upload_plan(cv_bound* h, HostPlan& o, int mode, ConvPlan& out) {
-  int4 *mt = nullptr, *kt = nullptr, *nt = nullptr;
-  int* ku = nullptr;
-  float* wm = nullptr;
+// The tables of a plan, in one allocation and copy.
+int upload_plan(cv_bound* h, HostPlan& o, HostReg& hr, int mode, ConvPlan& out) {
+  std::vector<int4> all;
+  auto put = [&](const void* src, size_t bytes) {
+    const size_t at = all.size();
+    all.resize(at + (bytes + 15) / 16, make_int4(0, 0, 0, 0));
+    if (bytes) std::memcpy(&all[at], src, bytes);
+    return at;
+  };
+  const size_t mt = put(o.mt.data(), o.mt.size() * sizeof(int4)), kt = put(o.kt.data(), o.kt.size() * sizeof(int4)),
+               nt = put(o.nt.data(), o.nt.size() * sizeof(int4)), ku = put(o.ku.data(), o.ku.size() * sizeof(int)),
+               wm = put(o.wm.data(), o.wm.size() * sizeof(float)), ob = put(hr.ob.data(), hr.ob.size() * sizeof(int4)),
+               w4 = put(hr.w4.data(), hr.w4.size() * sizeof(float4)), xt = put(hr.xt.data(), hr.xt.size() * sizeof(int2));
+  int4* d = nullptr;
   int rc;
-  if ((rc = h->mem.upload(&mt, o.mt.data(), o.mt.size(), nullptr)) ||
-      (rc = h->mem.upload(&kt, o.kt.data(), o.kt.size(), nullptr)) ||
-      (rc = h->mem.upload(&nt, o.nt.data(), o.nt.size(), nullptr)) ||
-      (!o.ku.empty() && (rc = h->mem.upload(&ku, o.ku.data(), o.ku.size(), nullptr))) ||
-      (rc = h->mem.upload(&wm, o.wm.data(), o.wm.size(), nullptr)))
-    return rc;
+  if ((rc = h->mem.upload(&d, all.data(), all.size(), nullptr))) return rc;
   out = o.p;
-  out.mtab = mt;
-  out.ktab = kt;
-  out.ntab = nt;
-  out.kuni = ku;
-  out.wm = wm;
+  out.mtab = d + mt;
+  out.ktab = d + kt;
+  out.ntab = d + nt;
+  out.kuni = o.ku.empty() ? nullptr : reinterpret_cast<const int*>(d + ku);
+  out.wm = reinterpret_cast<const float*>(d + wm);
   plan_finish(out);
   out.grid = conv_plan_grid(mode, out);
   conv_plan_sd(mode, out);
+  if (hr.ob.empty()) return CV_OK;
+  out.reg = hr.r;
+  out.reg.ob = d + ob;
+  out.reg.w4 = reinterpret_cast<const float4*>(d + w4);
+  out.reg.xt = hr.xt.empty() ? nullptr : reinterpret_cast<const int2*>(d + xt);
+  // a narrow output plane with a long K: the subdomain-major kernel splits the
+  // K passes over its idle waves; the same chunks here, so that every variant
+  // of the default path rounds alike
+  if (out.sd && out.nj <= 2) {
+    int& k = out.reg.ksp;
+    while (2 * k * (out.mpad >> 4) <= 8 && 2 * k <= (out.kpad >> 4)) k *= 2;
+  }
+  conv_plan_reg(mode, out);
+  out.reg.on = out.reg.grid > 0 && (out.reg.prefer || !out.sd);
   return CV_OK;
+}
+
+// Where bit `lane` of each word of the register-tile sign planes lies in the
+// staged input row of the forward plan pf, and which input it is (lanes
+// without an input: the spare slot).
+std::vector<int2> sign_slots(const ConvReg& r, const std::vector<int4>& ob, const ConvPlan& pf) {
+  std::vector<int2> xt((size_t)r.nwords * 64, make_int2(pf.dinp, 0));
+  const int plane = pf.gh * pf.gw;
+  for (int mt = 0; mt < r.n_mt; ++mt)
+    for (int t = 0; t < r.nt; ++t)
+      for (int rr = 0; rr < r.rc; ++rr)
+        for (int l = 0; l < 64; ++l) {
+          const int b = ob[(size_t)mt * 64 + l].y;
+          const int64_t j = b + (int64_t)r.plane * (rr + r.ts * t);
+          if (b < 0 || j >= pf.din) continue;
+          const int c = (int)(j / plane), y = (int)(j % plane) / pf.gw, x = (int)(j % plane) % pf.gw;
+          xt[(((size_t)mt * r.nt + t) * r.rc + rr) * 64 + l] =
+              make_int2(c * pf.pplane + pf.bofs + y * pf.gwp + x, (int)j);
+        }
+  return xt;
 }
 
 // Build the layer copies on the device.
@@ -755,9 +869,22 @@ int upload_layers(cv_bound* h, const cv_layer* layers, int n, hipStream_t s) {
       HostPlan pb, pf;
       plan_convt(ly, pb);
       plan_conv(ly, pf);
-      if ((rc = upload_plan(h, pb, i == 0 ? kBwdConc : kBwdRelax, d.bwd)) ||
-          (rc = upload_plan(h, pf, i == 0 ? kFwdX : kFwd, d.fwd)))
-        return rc;
+      HostReg rb, rf;
+      plan_reg(ly, true, pb, rb);
+      plan_reg(ly, false, pf, rf);
+      if ((rc = upload_plan(h, pb, rb, i == 0 ? kBwdConc : kBwdRelax, d.bwd))) return rc;
+      if (i == 0) {
+        // the first layer's adjoint step reads the sign planes in the order
+        // the concretisation's register tiles write them
+        rf.r.nwords = 0;
+        if (d.bwd.reg.on && !rf.ob.empty()) {
+          rf.xt = sign_slots(d.bwd.reg, rb.ob, pf.p);
+          rf.r.nwords = rb.r.nwords;
+          h->w64 = std::max(h->w64, rb.r.nwords);
+        }
+      }
+      if ((rc = upload_plan(h, pf, rf, i == 0 ? kFwdX : kFwd, d.fwd))) return rc;
+      if (i == 0) couple_first(d);
       d.bwd_def = d.bwd;
       d.fwd_def = d.fwd;
     }
@@ -1023,7 +1150,7 @@ int build(cv_bound* h, const cv_layer* layers, int n_layers, int P, const float*
   bt.m = m;
   bt.nd = nd;
   bt.d0 = h->d0;
-  bt.w64 = h->w64;
+  bt.w64 = h->w64;  // (as wide as the register-tile sign planes need)
   bt.ucount = d_ucount;
   bt.cidx = d_cidx;
   bt.chord = d_chord;
@@ -2227,6 +2354,10 @@ int grad_noalloc(cv_bound* h, const float* alpha, const float* beta, float* lb, 
   const size_t R = (size_t)std::max(1, h->R);
   const bool dense1 = h->layers[0].type == CV_LAYER_DENSE;
   const int ldx = r4(h->d0);
+  // the register tiles' sign planes may be wider than the input: a batch that
+  // fits only without them runs the first layer's older kernels
+  DevLayer& first = h->layers[0];
+  const int reg_b = first.bwd.reg.on, reg_f = first.fwd.reg.on, w64_reg = h->w64, w64_in = (h->d0 + 63) / 64;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -2237,13 +2368,19 @@ int grad_noalloc(cv_bound* h, const float* alpha, const float* beta, float* lb, 
   const size_t o_act1 = h->L >= 2 ? take(R * h->ldact * sizeof(float)) : 0;
   const size_t o_part = take(R * h->n_slots * sizeof(float));
   const size_t o_acomp = take((size_t)std::max<int64_t>(1, h->n_alpha) * sizeof(float));
-  const size_t o_xpos = take(R * h->w64 * sizeof(uint64_t));
-  const size_t o_xneg = take(R * h->w64 * sizeof(uint64_t));
   const bool need_xd = dense1 || h->l2;
   const size_t o_xd = need_xd ? take(R * ldx * sizeof(float)) : 0;
   const size_t o_perr = h->sound ? take(R * h->n_slots * sizeof(float)) : 0;
   const size_t o_psq = h->l2 ? take(R * h->n_slots * sizeof(float)) : 0;
   const size_t o_l2s = h->l2 ? take(R * sizeof(float)) : 0;
+  const size_t before = off;
+  size_t o_xpos = take(R * h->w64 * sizeof(uint64_t)), o_xneg = take(R * h->w64 * sizeof(uint64_t));
+  const bool narrow = off > kScratchBytes && w64_reg > w64_in;
+  if (narrow) {
+    off = before;
+    o_xpos = take(R * w64_in * sizeof(uint64_t));
+    o_xneg = take(R * w64_in * sizeof(uint64_t));
+  }
   if (off > kScratchBytes)
     return fail(CV_ENOMEM, "cv_bound_grad_noalloc: this batch needs %zu bytes of workspace, the static array holds %zu",
                 off, kScratchBytes);
@@ -2270,8 +2407,15 @@ int grad_noalloc(cv_bound* h, const float* alpha, const float* beta, float* lb, 
     h->psq = reinterpret_cast<float*>(b + o_psq);
     h->l2s = reinterpret_cast<float*>(b + o_l2s);
   }
+  if (narrow) {
+    first.bwd.reg.on = first.fwd.reg.on = 0;
+    h->w64 = h->bt.w64 = w64_in;
+  }
   int rc = enqueue_bwd(h, alpha, beta, true, lb, nullptr, 0, s);
   if (!rc) rc = enqueue_fwd(h, alpha, beta, g_alpha, g_beta, nullptr, s);
+  first.bwd.reg.on = reg_b;
+  first.fwd.reg.on = reg_f;
+  h->w64 = h->bt.w64 = w64_reg;
   // sound mode: the float64 bound (its buffers were allocated when sound
   // mode was switched on)
   if (!rc && h->sound) rc = enqueue_bwd64(h, alpha, beta, lb, nullptr, 0, s);
@@ -2421,6 +2565,22 @@ void free_joint(cv_bound* h) {
   h->joint = nullptr;
 }
 
+// The conv kernels of a joint pass: its bounds feed its own relaxations, where
+// a constant summed in another order is another trajectory, so
+// back-substitution (and with it the first layer's sign planes) stays on the
+// row-order kernels; the adjoint above the first layer, whose sums over k do
+// not depend on the kernel, runs on register tiles (the K passes in one chunk,
+// as in the row-major kernel that also stores zbar).
+void joint_conv_plans(cv_bound* x) {
+  for (int i = 0; i < x->L; ++i) {
+    DevLayer& d = x->layers[i];
+    if (d.type != CV_LAYER_CONV2D) continue;
+    d.bwd.reg.on = 0;
+    if (i == 0) d.fwd.reg.on = 0;
+    d.fwd.reg.ksp = 1;
+  }
+}
+
 // The joint state of h, built from its kept init arguments on first use.
 int make_joint(cv_bound* h, hipStream_t s) {
   if (h->joint) return CV_OK;
@@ -2450,6 +2610,7 @@ int make_joint(cv_bound* h, hipStream_t s) {
     return rc;
   if (J->hm->n_alpha != h->n_alpha || J->hm->nnz != h->nnz) return fail(CV_EINVAL, "joint layout mismatch");
   cv_bound* hm = J->hm;
+  joint_conv_plans(hm);
   DevMem& M = J->mem;
   const size_t bnd = (size_t)std::max(1, B * nd);
   if ((rc = ensure_grad(hm)) || (rc = hm->mem.alloc(&hm->zchord, hm->n_alpha)) ||
@@ -2500,6 +2661,7 @@ int make_joint(cv_bound* h, hipStream_t s) {
                     ident.data(), ptr.data(), sl.data(), sn.data(), ss.data(), s)))
       return rc;
     cv_bound* x = Q.h;
+    joint_conv_plans(x);
     Q.n_ash = x->n_alpha / Q.d;  // 2 uc_b per subdomain
     const int64_t nb = Q.nnz * 2 * Q.d;
     if ((rc = ensure_grad(x)) || (rc = x->mem.alloc(&x->zchord, x->n_alpha)) ||
@@ -2952,6 +3114,8 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
   }
   // conv layers: each kernel variant timed per layer and direction on this
   // batch (the same operands as a gradient pass)
+  float first_ms[2][kNumConvVariants];
+  int first_best[2] = {-1, -1};
   for (int dir = 0; dir < 2; ++dir) {
     for (int i = 1; i < L; ++i) {
       DevLayer& ly = h->layers[i - 1];
@@ -2986,6 +3150,8 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
       const ConvPlan def = dir == 0 ? ly.bwd_def : ly.fwd_def;
       float best_ms = 1e30f;
       int best = -1;
+      float times[kNumConvVariants];
+      std::fill(times, times + kNumConvVariants, 1e30f);
       for (int var = 0; var < kNumConvVariants; ++var) {
         ConvPlan pl = def;
         if (conv_plan_variant(mode, pl, var)) continue;
@@ -2999,15 +3165,33 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
         HIPCHK(hipEventSynchronize(e1));
         float ms = 0;
         HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-        if (ms < best_ms) {
+        times[var] = ms;
+        // (a first layer's register tiles are chosen for both directions together, below)
+        if (ms < best_ms && !(i == 1 && pl.reg.on)) {
           best_ms = ms;
           best = var;
         }
+      }
+      if (i == 1) {
+        first_best[dir] = best;
+        std::copy(times, times + kNumConvVariants, first_ms[dir]);
+        continue;
       }
       if (best >= 0) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         g_conv_tune[conv_key(mode, h->R, ly.g)] = best;
       }
+    }
+  }
+  if (L >= 2 && h->layers[0].type == CV_LAYER_CONV2D) {
+    // the first layer's two directions share the sign planes' order
+    const float reg = first_ms[0][2] + first_ms[1][2];
+    float old = 0.f;
+    for (int dir = 0; dir < 2; ++dir) old += first_best[dir] >= 0 ? first_ms[dir][first_best[dir]] : 1e30f;
+    for (int dir = 0; dir < 2; ++dir) {
+      const int v = reg < old ? 2 : first_best[dir];
+      std::lock_guard<std::mutex> lk(g_tune_mu);
+      if (v >= 0) g_conv_tune[conv_key(conv_mode(0, dir == 0, false), h->R, h->layers[0].g)] = v;
     }
   }
   assign_conv_variants(h, -1);
@@ -3091,7 +3275,7 @@ int cv_bound_conv_variant(const cv_bound* h, int32_t layer, int32_t dir) {
   const DevLayer& d = h->layers[layer - 1];
   if (d.type != CV_LAYER_CONV2D) return -1;
   const ConvPlan& pl = dir == 0 ? d.bwd : d.fwd;
-  return (pl.sd ? 2 : 0) + (pl.wg ? 1 : 0);
+  return pl.reg.on ? 2 : (pl.sd ? 2 : 0) + (pl.wg ? 1 : 0);
 }
 
 int cv_bound_set_tiling(cv_bound* h, int32_t tiling) {

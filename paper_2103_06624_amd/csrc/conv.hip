@@ -1169,15 +1169,12 @@ const void* sd_kernel_mode(int mode, int nt, bool wg, int nj, int ni) {
   }
 }
 
-// Work-unit size: all of a subdomain's rows when there are few (the
-// verification specs), else 16 (the identity specs of the root bounds).
-inline int sd_unit_rows(int m) { return m <= 32 ? m : 16; }
-
 template <int MODE, int NT, bool WG>
 int launch_sd(const ConvArgs& a, hipStream_t st) {
-  const int mu = sd_unit_rows(a.bt.m);
+  const int wgs = a.pl.grid_sd > 0 ? a.pl.grid_sd : 256;
+  const int mu = conv_unit_rows(a.M / a.bt.m, a.bt.m, wgs);
   const int n_units = (a.M / a.bt.m) * ((a.bt.m + mu - 1) / mu);
-  const dim3 grid(std::min(n_units, a.pl.grid_sd > 0 ? a.pl.grid_sd : 256)), block(kSdThreads);
+  const dim3 grid(std::min(n_units, wgs)), block(kSdThreads);
 #define CVB_SDL(J, I)                                                                                            \
   if (a.pl.nj == J && a.pl.ni == I) {                                                                           \
     launch_k(conv_sd<MODE, NT, WG, J, I>, grid, block, a.pl.smem_sd, st, a.in, a.ldi, a.pl, a.M, a.last, a.bt, a.v, \
@@ -1200,6 +1197,7 @@ int launch_sd(const ConvArgs& a, hipStream_t st) {
 template <int MODE>
 int dispatch(const ConvArgs& a, hipStream_t st) {
   if (a.M <= 0) return 0;
+  if (a.pl.reg.on && launch_conv_reg(MODE, a, st) == 0) return 0;
   // the subdomain-major kernel where an instantiation of this mode holds the
   // plan (a plan built for one mode may be launched in another: over an l2
   // ball the first layer's adjoint reads A(0) rows instead of sign planes),
@@ -1216,6 +1214,20 @@ int dispatch(const ConvArgs& a, hipStream_t st) {
 }
 
 }  // namespace
+
+int conv_unit_rows(int B, int m, int grid) {
+  int mu = 1;
+  int64_t best = INT64_MAX;
+  for (int u = 1; u <= std::min(m, 32); ++u) {
+    const int64_t units = (int64_t)B * ((m + u - 1) / u);
+    const int64_t cost = (units + grid - 1) / grid * (u + 1);
+    if (cost <= best) {
+      best = cost;
+      mu = u;
+    }
+  }
+  return mu;
+}
 
 int conv_plan_smem(const ConvPlan& pl) {
   return ((pl.wg ? 0 : pl.kpad * pl.nt * 16) + ((pl.dinp + 3) & ~3) + pl.dout) * (int)sizeof(float) +
@@ -1243,8 +1255,10 @@ int conv_plan_variant(int mode, ConvPlan& pl, int variant) {
   q.smem = conv_plan_smem(q);
   q.grid = conv_plan_grid(mode, q);
   conv_plan_sd(mode, q);
-  if (q.smem > 65536 || (sd && (!q.nj || q.smem_sd > 65536 || q.grid_sd <= 0)) || (!sd && q.grid <= 0)) return -1;
-  q.sd = sd;
+  const bool sd_ok = q.nj && q.smem_sd <= 65536 && q.grid_sd > 0;
+  q.reg.on = variant == 2 && q.reg.grid > 0 && (q.reg.prefer || !sd_ok);
+  if (!q.reg.on && (q.smem > 65536 || (sd && !sd_ok) || (!sd && q.grid <= 0))) return -1;
+  q.sd = sd && sd_ok;
   pl = q;
   return 0;
 }

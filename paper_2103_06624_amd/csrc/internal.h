@@ -77,7 +77,28 @@ struct ConvGeom {
 // staged[m.x + k.x] with no range check.  D[m, n] is
 // output[n.z + (osy * m.z + n.x) * ow + (osx * m.w + n.y)] when that lies in
 // the oh x ow plane and n.z >= 0.  Device tables, built once per layer.
+// The register-tile kernel's view of a plan (conv_reg.hip): the same GEMM with
+// its columns reordered so that a lane's four columns of a tile, and its
+// column tiles t, are the neurons base + plane (r + ts t) of a row (neurons
+// past dout do not exist).  Columns are (t, g, r), lane group g = lane / 16:
+// stride-2 transposed convolutions (class g, channel 4 t + r), paired outputs
+// (parity g mod 2, channel r + 4 (g / 2)), else channel 16 t + 4 g + r.
+struct ConvReg {
+  const int4* ob = nullptr;    // [n_mt 64] gather origin x and first neuron y (-1: none) of a lane; null: no such plan
+  const float4* w4 = nullptr;  // [kpad / 16][nt][64] the weights of four K steps
+  const int2* xt = nullptr;    // adjoint from x*: [nwords 64] staged slot and input of each sign bit
+  int n_mt, nt, plane, ts;
+  int ksp;             // chunks of the K passes, accumulated apart and added in order
+  int rc, nwords;      // concretisation: used r, and 64-bit words (mtile, t, r) per sign plane
+  int ntw, tm, nw;     // column and row tiles per wave, waves per workgroup
+  int np;              // K passes compiled in (0: a loop)
+  int nbuf, v4;        // staged rows in LDS; whether rows are staged by float4s
+  int grid, smem;
+  int prefer;          // measured better than the older kernels for such a layer
+  int on;              // whether launches use it
+};
 struct ConvPlan {
+  ConvReg reg;
   const int4* mtab;  // [mpad] gather offset x and output origin (z, w) of GEMM row m
   const int4* ktab;  // [kpad] gather offset x of GEMM column k
   const int4* ntab;  // [16 nt] output offset (x, y) and channel base z (-1: padding)
@@ -125,7 +146,18 @@ void conv_plan_sd(int mode, ConvPlan& pl);
 // row-major reading them from global memory, 2 and 3 the subdomain-major
 // kernel likewise.  Rebuilds the LDS size and grids; -1 (plan unchanged)
 // when the variant cannot run this layer.
+// (2 runs the register-tile kernel of conv_reg.hip where the plan has one)
 constexpr int kNumConvVariants = 4;
+// Rows of a subdomain per work unit of the subdomain-major kernels, whose
+// `grid` workgroups take the units in turn: the unit size with the fewest
+// rounds of rows, a unit's start (the subdomain's relaxation is loaded once per
+// unit) counted as one row.  All rows of a subdomain where the subdomains fill
+// the chip, fewer where they do not: 128 subdomains of 9 rows, subdomain-major
+// kernel, 22.0 us as 128 units and 15.5 as more (8 -> 8 k4 s2), 32.5 and 21.4
+// (adjoint 8 -> 8 k3 s1).
+int conv_unit_rows(int B, int m, int grid);
+void conv_plan_reg(int mode, ConvPlan& pl);
+int launch_conv_reg(int mode, const ConvArgs& a, hipStream_t s);  // -1: no such plan
 int conv_plan_variant(int mode, ConvPlan& pl, int variant);
 int launch_convt_bwd(int mode, const ConvArgs& a, hipStream_t s);
 int launch_conv_fwd(int mode, const ConvArgs& a, hipStream_t s);

@@ -1,0 +1,124 @@
+"""GPU parity of the conv layers on networks whose planes, channels, kernels and
+strides meet the edges of the register-tile kernel (conv_reg.hip): rows that are
+no whole float4s, one to five input channels, channel counts that leave part of
+a column tile empty, outputs in pairs and not, K passes compiled in and not,
+strides that it does not take, and batches of a few rows.  Bounds, gradients,
+the network at x* and a short optimisation against the FP64 oracle, over boxes
+and l2 balls.  Bar: 1e-4 guarded relative, as for the other parity tests."""
+import numpy as np
+import pytest
+
+from oracle import batch as ob
+from oracle import beta_crown as bc
+from paper_2103_06624_amd import synth
+from tests import cases
+from tests.cases import guarded_rel
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-4
+
+# input (c, h, w), convolutions (c_out, k, s, p), hidden dense width
+NETS = [
+    ((1, 9, 9), [(3, 3, 2, 1)], 16),                              # one channel, one row tile
+    ((3, 13, 17), [(6, 5, 2, 1), (9, 3, 1, 1)], 20),              # odd rows; 6 channels in pairs, 9 alone
+    ((3, 32, 32), [(16, 4, 2, 1), (5, 4, 2, 1)], 20),             # four column tiles; 19 row tiles, four K passes
+    ((2, 16, 16), [(8, 3, 1, 1), (8, 3, 1, 1), (20, 3, 2, 1)], 30),  # stride-1 first layer; pairs; 20 outputs
+    ((5, 16, 16), [(12, 4, 2, 1), (24, 3, 1, 0)], 30),            # two column tiles into the input
+    ((3, 12, 12), [(8, 4, 3, 1), (7, 2, 1, 0)], 20),              # stride 3: the older kernels
+    ((3, 32, 32), [(8, 4, 2, 1), (16, 4, 2, 1)], 24),             # chunks of the K passes
+]
+
+
+def build(i, n_dom, props=2):
+    shape, convs, fc = NETS[i]
+    rng = np.random.default_rng([77, i])
+    net = synth.cnn(rng, shape, convs, [fc, 10])
+    x0 = rng.uniform(0, 1, size=(props, net.dims[0])).astype(np.float32)
+    eps = 4.0 / 255.0
+    xlo, xhi = synth.box(x0, eps)
+    C = np.stack([synth.margin_spec(q, 10) for q in range(props)]).astype(np.float32)
+    net64 = bc.dense_net(net.layers)
+    # root bounds over the whole balls too: the box around x0, not clipped
+    lo64, up64 = ob.root_bounds_all(net64, x0 - eps, x0 + eps)
+    lo, up = bc.outward_f32(lo64, up64)
+    prop = (np.arange(n_dom) % props).astype(np.int32)
+    sp = synth.sample_splits(5 + i, net.dims, lo, up, prop, (0, 5))
+    args = (sp.dom_prop, sp.split_ptr, sp.layer, sp.neuron, sp.side)
+    orc = ob.OracleProblem(net.layers, xlo, xhi, C, lo, up, *args, net64=net64)
+    return net, xlo, xhi, x0, eps, C, lo, up, args, orc
+
+
+def dev(a):
+    return torch.from_numpy(np.asarray(a, np.float32)).cuda()
+
+
+def check(orc, pb, what):
+    alpha, beta = cases.random_vars(orc, seed=3)
+    a, b = dev(alpha), dev(beta)
+    ref = [orc.grad(d, alpha, beta) for d in range(orc.B)]
+    lb_ref = np.stack([r[0] for r in ref])
+    assert guarded_rel(pb.eval(a, b).cpu().numpy(), lb_ref).max() <= TOL, what
+    lb, ga, gb = (t.cpu().numpy() for t in pb.grad(a, b))
+    assert guarded_rel(lb, lb_ref).max() <= TOL, what
+    assert guarded_rel(ga, np.concatenate([r[1] for r in ref])).max() <= TOL, what
+    if orc.nnz:
+        assert guarded_rel(gb, np.concatenate([r[2].reshape(-1) for r in ref])).max() <= TOL, what
+    lbu, ub, _ = pb.upper(a, b)
+    up_ref = [orc.upper(d, alpha, beta) for d in range(orc.B)]
+    assert guarded_rel(lbu.cpu().numpy(), lb_ref).max() <= TOL, what
+    assert guarded_rel(ub.cpu().numpy(), np.stack([r[1] for r in up_ref])).max() <= TOL, what
+    a0, z0 = orc.default_alpha_flat(), np.zeros(orc.nnz * orc.m)
+    best, _ = pb.optimize(dev(a0), dev(z0), iters=3)
+    opt = np.stack([orc.optimize(d, a0, z0, bc.AdamConfig(iters=3))[0] for d in range(orc.B)])
+    assert guarded_rel(best.cpu().numpy(), opt).max() <= TOL, what
+
+
+@pytest.mark.parametrize("i", range(len(NETS)))
+@pytest.mark.parametrize("n_dom", [1, 7])
+def test_conv_tiles(i, n_dom):
+    from paper_2103_06624_amd.api import BoundProblem
+    print("conv tiles", NETS[i], n_dom, flush=True)
+    net, xlo, xhi, x0, eps, C, lo, up, args, orc = build(i, n_dom)
+    pb = BoundProblem(net.layers, xlo, xhi, C, lo, up, *args)
+    check(orc, pb, (NETS[i], n_dom, "box"))
+    pb.set_input_l2(x0, eps)
+    orc.set_l2(x0, np.full(x0.shape[0], np.float32(eps)))
+    check(orc, pb, (NETS[i], n_dom, "ball"))
+    pb.close()
+
+
+def test_largest_batch_of_the_static_workspace():
+    """The largest batch that the allocation-free gradient accepts (its first
+    layer may run another kernel there, for want of room) against the oracle
+    on its first and last subdomains."""
+    from paper_2103_06624_amd import binding as B
+    from paper_2103_06624_amd.api import BoundProblem
+    for n_dom in range(200, 60, -1):
+        net, xlo, xhi, _, _, C, lo, up, args, orc = build(6, n_dom) if n_dom == 200 else (net, xlo, xhi, 0, 0, C, lo, up,
+                                                                                         args, orc)
+        ptr = args[1][:n_dom + 1]
+        k = int(ptr[-1])
+        pb = BoundProblem(net.layers, xlo, xhi, C, lo, up, args[0][:n_dom], ptr, args[2][:k], args[3][:k], args[4][:k])
+        rng = np.random.default_rng(1)
+        a, b = dev(rng.uniform(0, 1, pb.n_alpha)), dev(rng.uniform(0, 0.5, pb.n_beta))
+        out = [torch.zeros(n, device="cuda") for n in (pb.n_rows, pb.n_alpha, pb.n_beta)]
+        try:
+            got = pb.grad_noalloc(a, b, *out)
+        except B.CvError as e:
+            assert e.code == B.CV_ENOMEM
+            pb.close()
+            continue
+        print("static workspace holds", n_dom, flush=True)
+        lb, ga, _ = (t.cpu().numpy() for t in got)
+        na, nb = orc.n_alpha, orc.nnz * orc.m
+        alpha = np.concatenate([a.cpu().numpy(), np.zeros(na - pb.n_alpha, np.float32)])
+        beta = np.concatenate([b.cpu().numpy(), np.zeros(nb - pb.n_beta, np.float32)])
+        for d in (0, n_dom - 1):
+            g, gal, _ = orc.grad(d, alpha, beta)
+            assert guarded_rel(lb[d], g).max() <= TOL
+            assert guarded_rel(ga[orc.alpha_off[d]:orc.alpha_off[d + 1]], gal).max() <= TOL
+        return
+    raise AssertionError("no batch fits the static workspace")
