@@ -271,13 +271,17 @@ namespace {
 std::mutex g_tune_mu;
 std::map<std::tuple<int, int, int, int>, int> g_tune;  // (mode, M, N, K) -> cfg
 
-// Untuned choice: small row tiles keep the chip full at these skinny shapes
-// (measured fastest for 200-wide layers at ~10^4 rows).
-int gemm_default_cfg(int M, int N) {
-  (void)M;
-  if (N <= 32) return 5;   // 32x32x16
-  if (N <= 256) return 6;  // 32x32x32
-  return 0;                // 64x64x16
+// Untuned choice.  32x32 tiles keep the chip full at these skinny shapes and
+// leave room for four and more waves per SIMD.  Up to 256 columns the K loop is
+// long against the epilogue and a second K slice in flight pays (9216 rows,
+// 200x200: adjoint 21.9 us against 22.9, relaxation 18.8 against 20.1).  Above,
+// the operands of the epilogue are most of the traffic, and registers for them
+// are worth more (100 -> 512 at 73728 rows: 217 us against 234; 64x64x16 tiles,
+// two waves per SIMD, 276; 100 -> 1024 at 18432 rows: 89 against 115).
+int gemm_default_cfg(int N) {
+  if (N <= 32) return 5;    // 32x32x16
+  if (N <= 256) return 19;  // 32x32x32, two slices in flight
+  return 6;                 // 32x32x32
 }
 
 int cfg_for(const cv_bound* h, int mode, int M, int N, int K, int fallback) {
@@ -296,8 +300,8 @@ void assign_tiles(cv_bound* h, int tiling) {
     if (h->layers[i - 1].type != CV_LAYER_DENSE) continue;
     const int N_b = h->dims[i - 1], K_b = h->dims[i];
     h->cfg[i - 1] =
-        tiling >= 0 ? tiling : cfg_for(h, i - 1 >= 1 ? kBwdRelax : kBwdConc, h->R, N_b, K_b, gemm_default_cfg(h->R, N_b));
-    h->cfg[n_layers + i - 1] = tiling >= 0 ? tiling : cfg_for(h, kFwd, h->R, K_b, N_b, gemm_default_cfg(h->R, K_b));
+        tiling >= 0 ? tiling : cfg_for(h, i - 1 >= 1 ? kBwdRelax : kBwdConc, h->R, N_b, K_b, gemm_default_cfg(N_b));
+    h->cfg[n_layers + i - 1] = tiling >= 0 ? tiling : cfg_for(h, kFwd, h->R, K_b, N_b, gemm_default_cfg(K_b));
   }
 }
 

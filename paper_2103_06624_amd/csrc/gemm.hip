@@ -39,16 +39,55 @@ __device__ __forceinline__ float4 mask4(float4 x, int row, int nrows, int k, int
   return x;
 }
 
+// Four consecutive values at p, of which the first nv exist: one 16-byte load
+// when `vec` (16-byte aligned, all four there or none), else one by one.
+template <class T>
+__device__ __forceinline__ void ld_quad(const T* __restrict__ p, bool vec, int nv, T (&x)[4]) {
+  static_assert(sizeof(T) == 4, "32-bit values");
+  if (vec) {
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (nv > 0) v = *reinterpret_cast<const uint4*>(p);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = __builtin_bit_cast(T, w[r]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = r < nv ? p[r] : T(0);
+  }
+}
+
+__device__ __forceinline__ void st_quad(float* p, bool vec, int nv, const float (&x)[4]) {
+  if (vec) {
+    if (nv > 0) *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (r < nv) p[r] = x[r];
+  }
+}
+
 // Epilogue operands of one tile, gathered before its K loop so that they land
-// while the MFMAs run.  Element (i, r, j) of a lane is row
-// m0 + wm*WM + 16i + 4(lane/16) + r, column n0 + wn*WN + 16j + lane%16.
-template <int BM, int BN>
+// while the MFMAs run.  In the backward modes (TR) the MFMAs compute each 16x16
+// block transposed (operands swapped: the same products, summed in the same
+// order), so element (i, j, r) of a lane is row m0 + wm*WM + 16i + lane%16,
+// column n0 + wn*WN + 16j + 4(lane/16) + r: a lane has one row per i and four
+// neighbouring columns per j, whose status words, chords, bias and results move
+// as 16-byte pieces (`vec`: widths and offsets in whole quads), and one row's
+// indices instead of four.  The epilogue's loads and index arithmetic, not the
+// MFMAs, take most of these launches: with 32x32x32 tiles 100 -> 1024 at 18432
+// rows went from 97.5 to 89.3 us, 100 -> 2048 at 9216 rows from 99.7 to 91.2,
+// 200 -> 784 with the concretisation at 9216 rows from 46.2 to 43.2.  The
+// adjoint keeps row 4(lane/16) + r, column lane%16: most of its traffic is the
+// packed alpha, its moments and the stored A, whose entries lie side by side
+// along a row and coalesce over the 16 lanes of one (transposed, 20 iterations
+// of 784-6x200-10 at 9216 rows take 6.31 ms instead of 6.02).
+template <int BM, int BN, bool TR>
 struct TileOps {
-  static constexpr int FM = BM / 32, FN = BN / 32, NE = FM * 4 * FN;
-  RowInfo eri[FM][4];
+  static constexpr int FM = BM / 32, FN = BN / 32, NE = FM * FN * 4;
+  RowInfo eri[FM][TR ? 1 : 4];
   uint32_t rec[NE];
   float2 ech[NE];
-  float ecf[NE], east[NE], ebias[FN];
+  float ecf[NE], east[NE], ebias[FN][TR ? 4 : 1];
   float ebe[NE];   // relaxation: beta of a split neuron (ecf holds alpha)
   float esw[NE];   // relaxation, sound mode: the neuron's rounding-error weight
   float2 emo[NE];  // adjoint with Adam: the moments of an unstable neuron's alpha
@@ -72,7 +111,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
   constexpr int QK = BK / 4;  // float4 per row of a slab
   constexpr int A_LD = (BM * QK + 255) / 256;  // float4 loads per thread
   constexpr int B_LD = (BN * QK + 255) / 256;
-  using Ops = TileOps<BM, BN>;
+  constexpr bool TR = MODE == kBwdRelax || MODE == kBwdConc;  // lane layout: see TileOps
+  using Ops = TileOps<BM, BN, TR>;
   __shared__ __attribute__((aligned(16))) float As[2][BM][LDK];
   __shared__ __attribute__((aligned(16))) float Bs[2][BN][LDK];
   __shared__ float red[2][BM];
@@ -138,36 +178,59 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].x, fb[j].x, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].y, fb[j].y, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].z, fb[j].z, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i].w, fb[j].w, acc[i][j], 0, 0, 0);
+          const float fx[4] = {fa[i].x, fa[i].y, fa[i].z, fa[i].w}, fy[4] = {fb[j].x, fb[j].y, fb[j].z, fb[j].w};
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(TR ? fy[t] : fx[t], TR ? fx[t] : fy[t], acc[i][j], 0, 0, 0);
         }
     }
   };
+
+  // (TR) whole quads: every lane's four columns all exist or none, 16-byte aligned
+  const bool vec = MODE == kBwdConc ? (N & 3) == 0 && (bt.d0 & 3) == 0
+                                    : (N & 3) == 0 && (bt.nd & 3) == 0 && (e.layer_off & 3) == 0;
+  auto row_of = [&](int i, int r) { return m0 + wm * WM + i * 16 + (TR ? csub : rsub + r); };
+  auto col_of = [&](int j, int r) { return n0 + wn * WN + j * 16 + (TR ? rsub + r : csub); };
+  auto elem = [&](int i, int j, int r) { return (i * FN + j) * 4 + r; };
+  // (TR) columns of quad j that exist in row i of the lane
+  auto count = [&](int i, int j) { return row_of(i, 0) < M ? min(max(N - col_of(j, 0), 0), 4) : 0; };
 
   // epilogue operands, first level: bias, row info and status records
   auto gather1 = [&](Ops& o) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
-      const int col = n0 + wn * WN + j * 16 + csub;
-      o.ebias[j] = (MODE != kBwdConc && col < N) ? e.bias[col] : 0.f;
+      if constexpr (TR) {
+        if (MODE != kBwdConc) ld_quad(e.bias + col_of(j, 0), vec, min(max(N - col_of(j, 0), 0), 4), o.ebias[j]);
+      } else {
+        o.ebias[j][0] = col_of(j, 0) < N ? e.bias[col_of(j, 0)] : 0.f;
+      }
     }
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm * WM + i * 16 + rsub + r;
-        o.eri[i][r] = row_info(bt, min(row, M - 1));
+    for (int i = 0; i < FM; ++i) {
+      if constexpr (TR) {
+        o.eri[i][0] = row_info(bt, min(row_of(i, 0), M - 1));
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          const int col = n0 + wn * WN + j * 16 + csub;
-          const int q = (i * 4 + r) * FN + j;
-          o.rec[q] = kInactive;
-          if (MODE != kBwdConc && row < M && col < N)
-            o.rec[q] = bt.status[(int64_t)o.eri[i][r].b * bt.nd + e.layer_off + col];
+          uint32_t w[4] = {kInactive, kInactive, kInactive, kInactive};
+          if (MODE != kBwdConc)
+            ld_quad(bt.status + (int64_t)o.eri[i][0].b * bt.nd + e.layer_off + col_of(j, 0), vec, count(i, j), w);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o.rec[elem(i, j, r)] = w[r];
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = row_of(i, r);
+          o.eri[i][r] = row_info(bt, min(row, M - 1));
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            const int col = col_of(j, r);
+            o.rec[elem(i, j, r)] =
+                row < M && col < N ? bt.status[(int64_t)o.eri[i][r].b * bt.nd + e.layer_off + col] : kInactive;
+          }
         }
       }
+    }
   };
   // second level, which needs the status records: chord and alpha / beta,
   // the stored A for the adjoint, or the box for concretisation
@@ -175,114 +238,120 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int j = 0; j < FN; ++j) {
+        const int q0 = elem(i, j, 0);
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int row = m0 + wm * WM + i * 16 + rsub + r;
-          const int col = n0 + wn * WN + j * 16 + csub;
-          const int q = (i * 4 + r) * FN + j;
-          const RowInfo& ri = o.eri[i][r];
-          o.ech[q] = make_float2(0.f, 0.f);
-          o.ecf[q] = 0.f;
-          o.east[q] = 0.f;
-          o.ebe[q] = 0.f;
-          o.esw[q] = 0.f;
-          o.emo[q] = make_float2(0.f, 0.f);
-          if (row >= M || col >= N) continue;
+        for (int r = 0; r < 4; ++r) {
+          o.ech[q0 + r] = make_float2(0.f, 0.f);
+          o.ecf[q0 + r] = o.east[q0 + r] = o.ebe[q0 + r] = o.esw[q0 + r] = 0.f;
+          o.emo[q0 + r] = make_float2(0.f, 0.f);
+        }
+        if constexpr (TR) {
+          const int nv = count(i, j);
+          const RowInfo& ri = o.eri[i][0];
           if (MODE == kBwdConc) {
-            const int64_t pb = (int64_t)ri.p * bt.d0 + col;
-            o.ech[q] = bt.l2x0 ? make_float2(bt.l2x0[pb], 0.f) : make_float2(bt.xlo[pb], bt.xhi[pb]);
+            const int64_t pb = (int64_t)ri.p * bt.d0 + col_of(j, 0);
+            float lo[4], hi[4] = {0.f, 0.f, 0.f, 0.f};
+            ld_quad((bt.l2x0 ? bt.l2x0 : bt.xlo) + pb, vec, nv, lo);
+            if (!bt.l2x0) ld_quad(bt.xhi + pb, vec, nv, hi);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o.ech[q0 + r] = make_float2(lo[r], hi[r]);
             continue;
           }
-          const int64_t pc = (int64_t)ri.p * bt.nd + e.layer_off + col;
-          const bool uns = (o.rec[q] & kKindMask) == kUnstable;
-          if (uns) o.ech[q] = bt.chord[pc];
-          if (MODE == kBwdRelax) {
-            relax_vars(bt, v, ri, o.rec[q], pc, &o.ecf[q], &o.ebe[q]);
-            if (bt.sw) o.esw[q] = bt.sw[pc];
-          } else if (uns && !v.sat) {
-            const int64_t ai = ri.abase + (o.rec[q] & kCidxMask);
-            o.east[q] = v.acomp[ai];
-            o.ecf[q] = v.alpha ? v.alpha[ai] : bt.adef[pc];
-            if (v.adam) o.emo[q] = make_float2(v.ma[ai], v.va[ai]);
+          const int64_t pc0 = (int64_t)ri.p * bt.nd + e.layer_off + col_of(j, 0);
+          bool any = false;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) any |= (o.rec[q0 + r] & kKindMask) == kUnstable;
+          if (any) {  // (chords are defined, zero, at stable neurons too)
+            const float* const cp = reinterpret_cast<const float*>(bt.chord + pc0);
+            float c[2][4];
+            ld_quad(cp, vec, min(2 * nv, 4), c[0]);
+            ld_quad(cp + 4, vec, max(2 * nv - 4, 0), c[1]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o.ech[q0 + r] = make_float2(c[r >> 1][2 * (r & 1)], c[r >> 1][2 * (r & 1) + 1]);
           }
-          // the fused top layer: ebe holds C_p W(L) at this neuron
-          if (MODE == kFwdTop) o.ebe[q] = e.cw[ri.p * e.cw_pstride + (int64_t)ri.k * e.ldcw + col];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (r >= nv) continue;
+            relax_vars(bt, v, ri, o.rec[q0 + r], pc0 + r, &o.ecf[q0 + r], &o.ebe[q0 + r]);
+            if (bt.sw) o.esw[q0 + r] = bt.sw[pc0 + r];
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = row_of(i, r), col = col_of(j, r), q = q0 + r;
+            const RowInfo& ri = o.eri[i][r];
+            if (row >= M || col >= N) continue;
+            const int64_t pc = (int64_t)ri.p * bt.nd + e.layer_off + col;
+            const bool uns = (o.rec[q] & kKindMask) == kUnstable;
+            if (uns) o.ech[q] = bt.chord[pc];
+            if (uns && !v.sat) {
+              const int64_t ai = ri.abase + (o.rec[q] & kCidxMask);
+              o.east[q] = v.acomp[ai];
+              o.ecf[q] = v.alpha ? v.alpha[ai] : bt.adef[pc];
+              if (v.adam) o.emo[q] = make_float2(v.ma[ai], v.va[ai]);
+            }
+            // the fused top layer: ebe holds C_p W(L) at this neuron
+            if (MODE == kFwdTop) o.ebe[q] = e.cw[ri.p * e.cw_pstride + (int64_t)ri.k * e.ldcw + col];
+          }
         }
+      }
+  };
+  // sum over the four lanes that share a row (lane % 16)
+  auto row_sum = [&](float x) {
+    x += __shfl_xor(x, 16, 64);
+    return x + __shfl_xor(x, 32, 64);
   };
 
-  // epilogue: lane holds rows 4*(lane/16)+r of each 16x16 block, column lane%16
+  // epilogue
   auto epilogue = [&](const Ops& o, floatx4 (&acc)[FM][FN]) {
-    if (MODE == kBwdRelax || MODE == kBwdConc) {
+    if constexpr (TR) {
       // second per-row sum: the rounding-error bound (sound mode) or, when
       // concretising over an l2 ball, the sum of A(0)^2; with both modes on,
       // the other array's slot gets 0 (the l2 concretisation's own rounding is
       // bounded at the final sum)
       float* const p2 = MODE == kBwdConc && bt.l2x0 ? e.psq : (e.perr ? e.perr : e.psq);
       float* const pz = e.perr && e.psq ? (p2 == e.perr ? e.psq : e.perr) : nullptr;
-      float cst[FM][4], cer[FM][4];
 #pragma unroll
       for (int i = 0; i < FM; ++i) {
+        float cst = 0.f, cer = 0.f;
+        const int row = row_of(i, 0);
+        const RowInfo& ri = o.eri[i][0];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          cst[i][r] = 0.f;
-          cer[i][r] = 0.f;
-          const int row = m0 + wm * WM + i * 16 + rsub + r;
-          const bool rok = row < M;
-          const RowInfo& ri = o.eri[i][r];
+        for (int j = 0; j < FN; ++j) {
+          const int nv = count(i, j);
+          float x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int j = 0; j < FN; ++j) {
-            const int col = n0 + wn * WN + j * 16 + csub;
-            const int q = (i * 4 + r) * FN + j;
+          for (int r = 0; r < 4; ++r) {
+            const int q = elem(i, j, r);
             const float a = acc[i][j][r];
-            const bool ok = rok && col < N;
+            if (r >= nv) continue;
             if (MODE == kBwdRelax) {
-              if (ok) {
-                if (v.acomp && (o.rec[q] & kKindMask) == kUnstable) v.acomp[ri.abase + (o.rec[q] & kCidxMask)] = a;
-                const float lam = relax_value(bt, v, ri, o.rec[q], o.ech[q], relax_pick(o.rec[q], o.ecf[q], o.ebe[q]),
-                                              a, o.ebias[j], &cst[i][r]);
-                e.out[(int64_t)row * e.ldo + col] = lam;
-                cer[i][r] = fmaf(fabsf(lam), o.esw[q], cer[i][r]);
-              }
+              if (v.acomp && (o.rec[q] & kKindMask) == kUnstable) v.acomp[ri.abase + (o.rec[q] & kCidxMask)] = a;
+              x[r] = relax_value(bt, v, ri, o.rec[q], o.ech[q], relax_pick(o.rec[q], o.ecf[q], o.ebe[q]), a,
+                                 o.ebias[j][r], &cst);
+              cer = fmaf(fabsf(x[r]), o.esw[q], cer);
             } else if (bt.l2x0) {  // l_p ball: A(0) x0 here, - eps ||A(0)||_q in the final sum
-              if (ok) {
-                cst[i][r] = fmaf(a, o.ech[q].x, cst[i][r]);
-                const float xd = lp_entry(a, bt.lpq, &cer[i][r]);
-                if (v.xdense) v.xdense[(int64_t)row * v.ldx + col] = xd;  // x*'s direction for the adjoint
-              }
+              cst = fmaf(a, o.ech[q].x, cst);
+              x[r] = lp_entry(a, bt.lpq, &cer);  // x*'s direction for the adjoint
             } else {
-              if (ok) {
-                const float tm = conc_term(a, o.ech[q].x, o.ech[q].y);
-                cst[i][r] += tm;
-                cer[i][r] = fmaf(bt.sg, fabsf(tm), cer[i][r]);
-              }
-              if (ok && v.xdense) v.xdense[(int64_t)row * v.ldx + col] = xstar(a > 0.f, a < 0.f, o.ech[q].x, o.ech[q].y);
-              if (v.xpos) {
-                const uint64_t mp = __ballot(ok && a > 0.f);
-                const uint64_t mn = __ballot(ok && a < 0.f);
-                const int cb = n0 + wn * WN + j * 16;
-                if (csub == 0 && rok && cb < N) {
-                  const int g = lane >> 4;
-                  reinterpret_cast<uint16_t*>(v.xpos + (int64_t)row * bt.w64)[cb >> 4] = (uint16_t)(mp >> (16 * g));
-                  reinterpret_cast<uint16_t*>(v.xneg + (int64_t)row * bt.w64)[cb >> 4] = (uint16_t)(mn >> (16 * g));
-                }
-              }
+              const float tm = conc_term(a, o.ech[q].x, o.ech[q].y);
+              cst += tm;
+              cer = fmaf(bt.sg, fabsf(tm), cer);
+              x[r] = xstar(a > 0.f, a < 0.f, o.ech[q].x, o.ech[q].y);
             }
           }
-          cst[i][r] = wave_sum16(cst[i][r]);
-          if (p2) cer[i][r] = wave_sum16(cer[i][r]);
+          if (MODE == kBwdRelax) st_quad(e.out + (int64_t)row * e.ldo + col_of(j, 0), vec, nv, x);
+          else if (v.xdense) st_quad(v.xdense + (int64_t)row * v.ldx + col_of(j, 0), vec, nv, x);
+        }
+        cst = row_sum(cst);
+        if (p2) cer = row_sum(cer);
+        if (rsub == 0) {
+          red[wn][wm * WM + i * 16 + csub] = cst;
+          if (p2) rede[wn][wm * WM + i * 16 + csub] = cer;
         }
       }
       // combine the two column halves (wn = 0, 1) of each row, one slot per tile
-      if (csub == 0) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            red[wn][wm * WM + i * 16 + rsub + r] = cst[i][r];
-            if (p2) rede[wn][wm * WM + i * 16 + rsub + r] = cer[i][r];
-          }
-      }
       __syncthreads();
       for (int t = tid; t < BM; t += 256) {
         const int row = m0 + t;
@@ -292,7 +361,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
           if (pz) pz[(int64_t)(e.slot0 + tn) * M + row] = 0.f;
         }
       }
-    } else if (MODE == kFwdTop) {
+    } else if constexpr (MODE == kFwdTop) {
       // last adjoint layer inside the optimiser: Adam step, then the next
       // iteration's top-layer relaxation with the new variables
       float cst[FM][4];
@@ -301,22 +370,22 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           cst[i][r] = 0.f;
-          const int row = m0 + wm * WM + i * 16 + rsub + r;
+          const int row = row_of(i, r);
           const bool rok = row < M;
           const RowInfo& ri = o.eri[i][r];
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
-            const int col = n0 + wn * WN + j * 16 + csub;
-            const int q = (i * 4 + r) * FN + j;
+            const int col = col_of(j, r);
+            const int q = elem(i, j, r);
             if (rok && col < N) {
               const float zb = e.wx0 ? fmaf(-v.l2s[row], acc[i][j][r], e.wx0[(int64_t)ri.p * N + col])
-                                     : acc[i][j][r] + o.ebias[j];
+                                     : acc[i][j][r] + o.ebias[j][0];
               const int64_t pc = (int64_t)ri.p * bt.nd + e.layer_off + col;
               float vn = 0.f;
               relax_fwd_value(bt, v, ri, o.rec[q], o.ech[q], o.east[q], o.ecf[q], pc, zb, true, o.emo[q], &vn);
               const float a = o.ebe[q];
               if (v.acomp && (o.rec[q] & kKindMask) == kUnstable) v.acomp[ri.abase + (o.rec[q] & kCidxMask)] = a;
-              e.top_out[(int64_t)row * e.ldo + col] = relax_value(bt, v, ri, o.rec[q], o.ech[q], vn, a, o.ebias[j],
+              e.top_out[(int64_t)row * e.ldo + col] = relax_value(bt, v, ri, o.rec[q], o.ech[q], vn, a, o.ebias[j][0],
                                                                   &cst[i][r]);
             }
           }
@@ -347,17 +416,17 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
       for (int i = 0; i < FM; ++i) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = m0 + wm * WM + i * 16 + rsub + r;
+          const int row = row_of(i, r);
           if (row >= M) continue;
           const RowInfo& ri = o.eri[i][r];
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
-            const int col = n0 + wn * WN + j * 16 + csub;
+            const int col = col_of(j, r);
             if (col >= N) continue;
-            const int q = (i * 4 + r) * FN + j;
+            const int q = elem(i, j, r);
             // l2 ball, first layer: W(1) x* + b(1) = (W(1) x0 + b(1)) - l2s (W(1) A(0))
             const float zb = e.wx0 ? fmaf(-v.l2s[row], acc[i][j][r], e.wx0[(int64_t)ri.p * N + col])
-                                   : acc[i][j][r] + o.ebias[j];
+                                   : acc[i][j][r] + o.ebias[j][0];
             if (v.sat) {  // the network itself at x*: every layer's output is kept
               e.out[(int64_t)row * e.ldo + col] = true_relu(o.rec[q], zb, v.sat + row);
               continue;
