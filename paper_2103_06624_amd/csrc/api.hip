@@ -84,6 +84,7 @@ struct DevLayer {
   int ld_in, ld_out;       // padded row lengths of W and Wt (dense)
   float* W = nullptr;      // dense [dout, ld_in]; conv OIHW
   float* Wt = nullptr;     // dense [din, ld_out]
+  double* W64 = nullptr;   // conv: W in conv64_rows_k's order (sound mode, large batches)
   float* bias = nullptr;   // [dout], per neuron
   ConvPlan bwd{}, fwd{};   // conv: back-substitution and forward implicit GEMMs
   ConvPlan bwd_def{}, fwd_def{};  // the same as first built (before any variant choice)
@@ -207,6 +208,7 @@ struct cv_bound {
   float* sw64 = nullptr;    // [P, nd]
   float* err064 = nullptr;  // [P, m]
   double sg64 = 0.0, scale64 = 1.0, ball64 = 0.0;
+  double2* chord64 = nullptr;  // [P, nd] chords in double (large batches)
   double* act64[2] = {nullptr, nullptr};
   double *part64 = nullptr, *perr64 = nullptr, *psq64 = nullptr;  // [L, R]
   // the optimiser in sound mode: each row's best float32 bound so far, the
@@ -1382,14 +1384,29 @@ void sound_weights(const cv_bound* h, const cv_layer* layers, const float* x_lo,
 // Sound mode's batch-sized buffers (float64 rows and partials, the optimiser's
 // best-iterate copies), from the batch pool at its capacities.
 int ensure_sound_batch(cv_bound* h) {
+  int rc;
+  if (h->R >= kRows64) {
+    bool packed = !h->chord64;
+    if (packed) {
+      const int64_t n = (int64_t)h->P * std::max(h->nd, 1);
+      if ((rc = h->mem.alloc(&h->chord64, n))) return rc;
+      launch_chord64(h->dl, h->du, h->chord64, (int64_t)h->P * h->nd, nullptr);
+    }
+    for (DevLayer& ly : h->layers) {
+      if (ly.type != CV_LAYER_CONV2D || ly.W64) continue;
+      if ((rc = h->mem.alloc(&ly.W64, conv64_pack_size(ly.g)))) return rc;
+      launch_conv64_pack(ly.W, ly.g, ly.W64, nullptr);
+      packed = true;
+    }
+    if (packed) HIPCHK(hipStreamSynchronize(nullptr));
+  }
   if (h->perr) return CV_OK;
   const cv_bound::Cap& c = h->bcap;
-  const int64_t R1 = std::max<int64_t>(1, c.R);
+  const int64_t R1 = std::max<int64_t>(1, c.R), R8 = R1 + 8;  // (the last group of rows is read whole)
   const int L = h->L;
-  int rc;
   if ((rc = h->bm.alloc(&h->perr, (size_t)R1 * h->n_slots)) ||
-      (rc = h->bm.alloc(&h->act64[0], (size_t)R1 * h->ldact)) ||
-      (rc = h->bm.alloc(&h->act64[1], (size_t)R1 * h->ldact)) || (rc = h->bm.alloc(&h->part64, (size_t)R1 * L)) ||
+      (rc = h->bm.alloc(&h->act64[0], (size_t)R8 * h->ldact)) ||
+      (rc = h->bm.alloc(&h->act64[1], (size_t)R8 * h->ldact)) || (rc = h->bm.alloc(&h->part64, (size_t)R1 * L)) ||
       (rc = h->bm.alloc(&h->perr64, (size_t)R1 * L)) || (rc = h->bm.alloc(&h->psq64, (size_t)R1 * L)) ||
       (rc = h->bm.alloc(&h->gbest, (size_t)R1)) || (rc = h->bm.alloc(&h->improved, (size_t)R1)) ||
       (rc = h->bm.alloc(&h->abest, (size_t)std::max<int64_t>(1, c.na))) ||
@@ -1727,6 +1744,7 @@ int enqueue_bwd64(cv_bound* h, const float* alpha, const float* beta, float* lb,
   q.bt = h->bt;
   q.l = h->dl;
   q.u = h->du;
+  q.chord = h->chord64;
   q.alpha = alpha;
   q.beta = beta;
   q.sw = h->sw64;
@@ -1769,6 +1787,7 @@ int enqueue_bwd64(cv_bound* h, const float* alpha, const float* beta, float* lb,
     y.N = h->dims[i - 1];
     y.W = ly.W;
     y.ldw = ly.ld_in;
+    y.w64 = ly.W64;
     y.conc = i == 1;
     y.slot = L - i;
     if (i >= 2) {

@@ -219,6 +219,7 @@ struct Pass64 {
   Batch bt;
   const float* l;      // [P, nd] root bounds (the chords are formed from them in double)
   const float* u;
+  const double2* chord;  // [P, nd] the chords in double (batches of kRows64 rows on)
   const float* alpha;  // [n_alpha] or null (default slopes)
   const float* beta;   // [nnz, m]
   const float* sw;     // [P, nd] weight of |Lambda_k| in the float64 rounding-error bound
@@ -253,6 +254,7 @@ struct Lay64 {
   int ldi;
   int K, N;          // d_i, d_(i-1)
   const float* W;    // dense [d_i, ldw]; conv OIHW
+  const double* w64; // conv: W packed by launch_conv64_pack (batches of kRows64 rows on), or null
   int ldw;
   int conc;          // 1: into the input (concretise)
   int layer_off;     // layer i-1 in the nd axis (relaxation)
@@ -270,6 +272,17 @@ struct Fin64 {
   float* best;
   int first;
 };
+// conv64_rows_k: Lambda's planes in LDS (pitch pw, padded plane, border b0
+// before the first entry), channels of the packed weights, and 2^32 / plane
+// and 2^32 / pw rounded up.
+struct Geo64 {
+  int pw, plane, b0, cip;
+  uint32_t m_plane, m_pw;
+};
+constexpr int kRows64 = 512;  // rows from which the several-row float64 kernels run (launch_conv64)
+void launch_chord64(const float* l, const float* u, double2* ch, int64_t n, hipStream_t s);
+size_t conv64_pack_size(const ConvGeom& g);
+void launch_conv64_pack(const float* W, const ConvGeom& g, double* dst, hipStream_t s);
 void launch_top64(const Pass64& q, const Top64& t, hipStream_t s);
 void launch_dense64(const Pass64& q, const Lay64& y, hipStream_t s);
 void launch_conv64(const Pass64& q, const Lay64& y, const ConvGeom& g, hipStream_t s);

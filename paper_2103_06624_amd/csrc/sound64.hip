@@ -12,9 +12,9 @@
 // float: the reported bound lies below the exact bound of the same relaxation
 // by that margin (about 1e-13 of the terms' magnitudes) plus one float ulp.
 //
-// One workgroup per batch row for the dense and convolution layers (four
-// rows per workgroup for dense layers on large batches; the rows' inputs in
-// LDS), one wave per row for the top layer.  These kernels run once per evaluation in sound
+// One workgroup per batch row for the dense and convolution layers (the rows'
+// inputs in LDS), on large batches three rows of a subdomain; one wave per row
+// for the top layer.  These kernels run once per evaluation in sound
 // mode, not in the optimiser's loop.
 #include "common.h"
 #include "internal.h"
@@ -185,6 +185,110 @@ __device__ __forceinline__ void epi64(const Pass64& q, const RowInfo& ri, const 
   }
 }
 
+// The same for kC outputs j0 + st u (u < nu) in kR rows of one subdomain,
+// row0 .. row0 + nr - 1 (nr uniform over the workgroup): everything the
+// epilogue reads is read ahead of the products -- what the rows share (status
+// word, chord in double, weights, bias, or the box) once for all of them --
+// and relax64's (conc64's) arithmetic then runs on registers, as selects.
+template <int kC, int kR>
+struct Epi64 {
+  uint32_t rec[kC];
+  float sw[kC], bias[kC], var[kR][kC];  // var: alpha (unstable) or beta (split); (concretisation: sw, bias the box)
+  double2 ch[kC];
+
+  // (loads are unconditional, outputs that do not exist read j0's operands and
+  // neurons without a variable their weight: a load under a branch of its own
+  // is waited for at the branch's end, one after the other)
+  __device__ __forceinline__ void read(const Pass64& q, const Lay64& y, int row0, int nr, int j0, int st, int nu) {
+    const int b = row0 / q.bt.m, k0 = row0 - b * q.bt.m, p = q.bt.prop[b];
+    if (y.conc) {
+      const float* const lo = (q.bt.l2x0 ? q.bt.l2x0 : q.bt.xlo) + (int64_t)p * q.bt.d0 + j0;
+      const float* const hi = (q.bt.l2x0 ? q.bt.l2x0 : q.bt.xhi) + (int64_t)p * q.bt.d0 + j0;
+#pragma unroll
+      for (int u = 0; u < kC; ++u) {
+        sw[u] = lo[u < nu ? st * u : 0];
+        bias[u] = hi[u < nu ? st * u : 0];
+      }
+      return;
+    }
+    const int64_t pc0 = (int64_t)p * q.bt.nd + y.layer_off + j0;
+#pragma unroll
+    for (int u = 0; u < kC; ++u) {
+      const int d = u < nu ? st * u : 0;
+      rec[u] = q.bt.status[(int64_t)b * q.bt.nd + y.layer_off + j0 + d];
+      sw[u] = q.sw[pc0 + d];
+      bias[u] = y.bias[j0 + d];
+      ch[u] = q.chord[pc0 + d];
+    }
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      const int rr = r < nr ? r : 0;
+      const int64_t ab = q.bt.rbase[row0 + rr];
+#pragma unroll
+      for (int u = 0; u < kC; ++u) {
+        const uint32_t kind = rec[u] & kKindMask;
+        const int64_t pc = pc0 + (u < nu ? st * u : 0);
+        const float* v = q.alpha ? q.sw + pc : q.bt.adef + pc;
+        v = q.alpha && kind == kUnstable ? q.alpha + (ab + (rec[u] & kCidxMask)) : v;
+        v = kind == kSplit ? q.beta + ((int64_t)(rec[u] & kSplitMask) * q.bt.m + k0 + rr) : v;
+        var[r][u] = *v;
+      }
+    }
+  }
+
+  __device__ __forceinline__ void apply(const Pass64& q, const Lay64& y, int row0, int nr, int j0, int st, int nu,
+                                        const double (&a)[kR][kC], double (&cst)[kR], double (&err)[kR],
+                                        double (&sq)[kR]) const {
+    if (y.conc) {
+#pragma unroll
+      for (int r = 0; r < kR; ++r) {
+        if (r >= nr) break;
+#pragma unroll
+        for (int u = 0; u < kC; ++u) {
+          if (u >= nu) continue;
+          const double av = a[r][u];
+          if (q.bt.l2x0) {
+            cst[r] += av * (double)sw[u];
+            sq[r] += av * av;
+          } else {
+            const double tm = fmin(av * (double)sw[u], av * (double)bias[u]);
+            cst[r] += tm;
+            err[r] += q.sg * fabs(tm);
+          }
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      if (r >= nr) break;
+      double* const out = y.out + (int64_t)(row0 + r) * y.ldo + j0;
+#pragma unroll
+      for (int u = 0; u < kC; ++u) {
+        const double av = a[r][u], vr = var[r][u];
+        const uint32_t kind = u < nu ? rec[u] & kKindMask : kInactive;
+        const bool neg = kind == kUnstable && !(av >= 0.0);
+        double lam = kind == kActive ? av : 0.0;
+        lam = kind == kUnstable ? (neg ? av * ch[u].x : vr * av) : lam;
+        lam = kind == kSplit ? ((rec[u] & kSidePos) ? av - vr : vr) : lam;
+        cst[r] += neg ? av * ch[u].y : 0.0;
+        cst[r] += lam * (double)bias[u];
+        err[r] += fabs(lam) * (double)sw[u];
+        if (u < nu) out[st * u] = lam;
+      }
+    }
+  }
+};
+
+// Chords of every neuron in double, u/(u-l) and -ul/(u-l) (the difference of
+// two floats is exact): what relax64 forms at each use.
+__global__ void chord64_k(const float* __restrict__ l, const float* __restrict__ u, double2* __restrict__ ch, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double lv = l[i], uv = u[i], den = uv - lv;
+  ch[i] = den > 0.0 ? make_double2(uv / den, -(uv * lv) / den) : make_double2(0.0, 0.0);
+}
+
 // The top ReLU layer: A(L-1) = C_p W(L) in double (general specification) or
 // the exact rows +-W(L) (identity specification, as float rows CW), relaxed
 // (or concretised when there is no ReLU layer).  One wave per row.
@@ -257,74 +361,81 @@ __global__ __launch_bounds__(256) void dense64_k(Pass64 q, Lay64 y) {
   }
 }
 
-// The same for kDenseRows consecutive rows per workgroup (rpb, all of them
-// in LDS), so that each weight read serves every one of them, on large
-// batches; each row's sums keep the one-row order.
-constexpr int kDenseRows = 4;
-__global__ __launch_bounds__(256) void dense64_rows_k(Pass64 q, Lay64 y, int rpb) {
-  extern __shared__ double lam_s[];
-  __shared__ double red[4];
-  const int row0 = blockIdx.x * rpb;
-  const int nr = min(rpb, q.bt.n_rows - row0);
-  const int tot = nr * y.K;
-  for (int t0 = threadIdx.x; t0 < tot; t0 += 256 * 8) {
-    double v[8];
+// The rows' sums over a workgroup's threads, to their slots: within each wave,
+// then (red: 3 kR NW doubles) over its NW waves.
+template <int kR, int NW>
+__device__ __forceinline__ void block_out64(const Pass64& q, int slot, int row0, int nr, double (&cst)[kR],
+                                            double (&err)[kR], double (&sq)[kR], double* red) {
+  const int wid = threadIdx.x >> 6;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = t0 + 256 * u, r = t / y.K;
-      v[u] = t < tot ? y.in[(int64_t)(row0 + r) * y.ldi + (t - r * y.K)] : 0.0;
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      cst[r] += __shfl_xor(cst[r], o, 64);
+      err[r] += __shfl_xor(err[r], o, 64);
+      if (q.psq) sq[r] += __shfl_xor(sq[r], o, 64);
     }
+  if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (t0 + 256 * u < tot) lam_s[t0 + 256 * u] = v[u];
+    for (int r = 0; r < kR; ++r) {
+      red[(3 * r) * NW + wid] = cst[r];
+      red[(3 * r + 1) * NW + wid] = err[r];
+      red[(3 * r + 2) * NW + wid] = sq[r];
+    }
   }
   __syncthreads();
-  double cst[kDenseRows], err[kDenseRows], sq[kDenseRows];
-  RowInfo ri[kDenseRows];
+  for (int t = threadIdx.x; t < 3 * nr; t += 64 * NW) {
+    double v = red[NW * t];
 #pragma unroll
-  for (int r = 0; r < kDenseRows; ++r) {
-    cst[r] = err[r] = sq[r] = 0.0;
-    if (r < nr) ri[r] = row_info(q.bt, row0 + r);
+    for (int i = 1; i < NW; ++i) v += red[NW * t + i];
+    const int r = t / 3, c = t - 3 * r;
+    const int64_t o = (int64_t)slot * q.bt.n_rows + row0 + r;
+    if (c == 0) q.part[o] = v;
+    else if (c == 1) q.perr[o] = v;
+    else if (q.psq) q.psq[o] = v;
   }
-  constexpr int kC = 2;
-  for (int j0 = threadIdx.x; j0 < y.N; j0 += 256 * kC) {
-    double a[kDenseRows][kC];
+}
+
+// First row and rows (at most kR) of workgroup blockIdx.x: a subdomain's rows
+// in groups of kR.
+template <int kR>
+__device__ __forceinline__ void row_group(int m, int* row0, int* nr) {
+  const int per = (m + kR - 1) / kR, b = blockIdx.x / per, k0 = (blockIdx.x - b * per) * kR;
+  *row0 = b * m + k0;
+  *nr = min(kR, m - k0);
+}
+
+// The same for up to kR rows of one subdomain per workgroup, on large batches.
+// In the one-row kernel a product takes a load and a conversion of its weight;
+// here both serve kR rows, and Lambda, the same for every lane, is read by
+// scalar loads.  100 -> 512 at 9216
+// rows: 130 us in the one-row kernel, 65 here (nine rows 154, five 101: fewer
+// waves fit).  Each row's sums over k keep the one-row order.
+template <int kR, int NW>
+__global__ __launch_bounds__(64 * NW) void dense64_rows_k(Pass64 q, Lay64 y, const double* __restrict__ in,
+                                                          const float* __restrict__ W) {
+  __shared__ double red[3 * kR * NW];
+  int row0, nr;
+  row_group<kR>(q.bt.m, &row0, &nr);
+  double cst[kR], err[kR], sq[kR];
 #pragma unroll
-    for (int r = 0; r < kDenseRows; ++r)
+  for (int r = 0; r < kR; ++r) cst[r] = err[r] = sq[r] = 0.0;
+  const double* const lam = in + (int64_t)row0 * y.ldi;  // (whole groups readable; results past nr are dropped)
+  for (int j = threadIdx.x; j < y.N; j += 64 * NW) {
+    Epi64<1, kR> ep;
+    ep.read(q, y, row0, nr, j, 0, 1);
+    double a[kR][1];
 #pragma unroll
-      for (int u = 0; u < kC; ++u) a[r][u] = 0.0;
+    for (int r = 0; r < kR; ++r) a[r][0] = 0.0;
+#pragma unroll 8
     for (int k = 0; k < y.K; ++k) {
-      double w[kC];
+      const double w = (double)W[(int64_t)k * y.ldw + j];
 #pragma unroll
-      for (int u = 0; u < kC; ++u) {
-        const int j = j0 + 256 * u;
-        w[u] = j < y.N ? (double)y.W[(int64_t)k * y.ldw + j] : 0.0;
-      }
-#pragma unroll
-      for (int r = 0; r < kDenseRows; ++r) {
-        if (r < nr) {
-          const double l = lam_s[r * y.K + k];
-#pragma unroll
-          for (int u = 0; u < kC; ++u) a[r][u] += l * w[u];
-        }
-      }
+      for (int r = 0; r < kR; ++r) a[r][0] = fma(lam[(int64_t)r * y.ldi + k], w, a[r][0]);
     }
-#pragma unroll
-    for (int r = 0; r < kDenseRows; ++r)
-      if (r < nr) epi64<kC>(q, ri[r], y, row0 + r, j0, a[r], cst[r], err[r], sq[r]);
+    ep.apply(q, y, row0, nr, j, 0, 1, a, cst, err, sq);
   }
-#pragma unroll
-  for (int r = 0; r < kDenseRows; ++r) {
-    if (r < nr) {  // nr is uniform over the workgroup
-      const double c = block_sum_d(cst[r], red), e = block_sum_d(err[r], red), s2 = block_sum_d(sq[r], red);
-      if (threadIdx.x == 0) {
-        const int64_t o = (int64_t)y.slot * q.bt.n_rows + row0 + r;
-        q.part[o] = c;
-        q.perr[o] = e;
-        if (q.psq) q.psq[o] = s2;
-      }
-    }
-  }
+  block_out64<kR, NW>(q, y.slot, row0, nr, cst, err, sq, red);
 }
 
 // a[U] = f(U) for the constant indices U (the array stays in registers).
@@ -511,6 +622,124 @@ __global__ __launch_bounds__(256) void conv64_k(Pass64 q, Lay64 y, ConvGeom g) {
   }
 }
 
+// The weights of a conv layer in double, [ky][kx][co][cip] (input channel
+// innermost, zero past ci), for conv64_rows_k.
+__global__ void conv64_pack_k(const float* __restrict__ W, ConvGeom g, int cip, double* __restrict__ dst) {
+  const int n = g.k * g.k * g.co * cip;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+    const int c = t % cip, r = t / cip, co = r % g.co, kk = r / g.co;
+    dst[t] = c < g.ci ? (double)W[(int64_t)(co * g.ci + c) * g.k * g.k + kk] : 0.0;
+  }
+}
+
+// Back-substitution through conv layer i for up to kR rows of one subdomain per
+// workgroup, on large batches.  The input positions whose coordinates agree modulo the stride meet
+// the same taps; a wave takes 64 positions of one such class and kC input
+// channels, so that every weight it needs is the same for all of its lanes and
+// comes from a scalar load, already in double, and each Lambda value read from
+// LDS serves kC products.  (In the one-row kernels a product takes an LDS read
+// and a conversion of its weight, and a wave whose lanes are neighbours in x
+// walks the taps of all classes.)  The rows lie in LDS inside a zero border, so
+// no tap needs a range check.  Eight waves share the rows'
+// planes (62 KB at 8x16x16: two workgroups per compute unit); four waves with
+// eight channels each run 2 per SIMD and take 159 us where these take 118.
+// At 9216 rows: 8x8x8 back to 8x16x16 168 us in the one-row kernel, 127 here,
+// 8x16x16 to itself 202 and 158, into 3x32x32 182 and 138; what is left is the
+// memory traffic (63 us of a 16x16 layer) and the phases of a workgroup that
+// two of them do not overlap.  Each output's sum keeps the order of tap_sum64.
+template <int kC, int kR, int NW>
+__global__ __launch_bounds__(64 * NW) void conv64_rows_k(Pass64 q, Lay64 y, ConvGeom g, Geo64 z,
+                                                     const double* __restrict__ in, const double* __restrict__ wt) {
+  extern __shared__ __attribute__((aligned(16))) double lam_s[];
+  __shared__ double red[3 * kR * NW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  int row0, nr;
+  row_group<kR>(q.bt.m, &row0, &nr);
+  const int rowlen = g.co * z.plane;  // (padded row of one batch row)
+  for (int t0 = tid; t0 < rowlen; t0 += 64 * NW * 4) {
+    double v[kR][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = min(t0 + 64 * NW * u, rowlen - 1);
+      const int co = __umulhi(t, z.m_plane), rem = t - co * z.plane, yy = __umulhi(rem, z.m_pw);
+      const int oy = yy - z.b0, ox = rem - yy * z.pw - z.b0;
+      const bool in_p = (unsigned)oy < (unsigned)g.ho && (unsigned)ox < (unsigned)g.wo;
+      const int k = in_p ? (co * g.ho + oy) * g.wo + ox : 0;
+#pragma unroll
+      for (int r = 0; r < kR; ++r) {
+        const double x = in[(int64_t)(row0 + min(r, nr - 1)) * y.ldi + k];
+        v[r][u] = in_p ? x : 0.0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (t0 + 64 * NW * u < rowlen) {
+#pragma unroll
+        for (int r = 0; r < kR; ++r) lam_s[r * rowlen + t0 + 64 * NW * u] = v[r][u];
+      }
+  }
+  __syncthreads();
+  double cst[kR], err[kR], sq[kR];
+#pragma unroll
+  for (int r = 0; r < kR; ++r) cst[r] = err[r] = sq[r] = 0.0;
+
+  // items (class, chunk of 64 positions, channel group), dealt round the waves
+  const int groups = (g.ci + kC - 1) / kC;
+  int item = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int ry = 0; ry < g.s; ++ry) {
+    const int iy0 = (ry + g.s - g.p % g.s) % g.s, ny = (g.hi - iy0 + g.s - 1) / g.s;
+    for (int rx = 0; rx < g.s; ++rx) {
+      const int ix0 = (rx + g.s - g.p % g.s) % g.s, nx = (g.wi - ix0 + g.s - 1) / g.s;
+      const int np = ny > 0 && nx > 0 ? ny * nx : 0, chunks = (np + 63) >> 6, n = chunks * groups;
+      for (; item < n; item += NW) {
+        const int chunk = item / groups, c0 = (item - chunk * groups) * kC;
+        const int e = min(chunk * 64 + lane, np - 1), ay = e / nx, ax = e - ay * nx;
+        const bool ok = chunk * 64 + lane < np;
+        const int iy = iy0 + g.s * ay, ix = ix0 + g.s * ax;
+        const int oy0 = (iy + g.p - ry) / g.s, ox0 = (ix + g.p - rx) / g.s;
+        const double* lp = lam_s + (oy0 + z.b0) * z.pw + ox0 + z.b0;
+        const int hw = g.hi * g.wi, j0 = c0 * hw + iy * g.wi + ix, nu = ok ? min(kC, g.ci - c0) : 0;
+        Epi64<kC, kR> ep;
+        ep.read(q, y, row0, nr, j0, hw, nu);
+        double a[kR][kC];
+#pragma unroll
+        for (int r = 0; r < kR; ++r)
+#pragma unroll
+          for (int c = 0; c < kC; ++c) a[r][c] = 0.0;
+        for (int ky = ry, ty = 0; ky < g.k; ky += g.s, ++ty)
+          for (int kx = rx, tx = 0; kx < g.k; kx += g.s, ++tx) {
+            const double* const wp = wt + (int64_t)(ky * g.k + kx) * g.co * z.cip + c0;
+            const double* const l0 = lp - ty * z.pw - tx;
+#pragma unroll 2
+            for (int co = 0; co < g.co; ++co) {
+              double w[kC];
+#pragma unroll
+              for (int c = 0; c < kC; ++c) w[c] = wp[co * z.cip + c];
+#pragma unroll
+              for (int r = 0; r < kR; ++r) {
+                const double l = l0[r * rowlen + co * z.plane];
+#pragma unroll
+                for (int c = 0; c < kC; ++c) a[r][c] = fma(l, w[c], a[r][c]);
+              }
+            }
+          }
+        ep.apply(q, y, row0, nr, j0, hw, nu, a, cst, err, sq);
+      }
+      item -= n;  // the next class's items follow on
+    }
+  }
+  block_out64<kR, NW>(q, y.slot, row0, nr, cst, err, sq, red);
+}
+
+// Channels per wave item of conv64_rows_k.
+int conv64_channels(const ConvGeom& g) { return g.ci <= 3 ? 3 : 4; }
+
+template <int kC, int kR, int NW>
+void launch_conv64_rows(const Pass64& q, const Lay64& y, const ConvGeom& g, const Geo64& z, hipStream_t s) {
+  launch_k(conv64_rows_k<kC, kR, NW>, (unsigned)(q.bt.n_rows / q.bt.m * ((q.bt.m + kR - 1) / kR)), 64 * NW,
+           (uint32_t)((size_t)kR * g.co * z.plane * sizeof(double)), s, q, y, g, z, y.in, y.w64);
+}
+
 // Round a double down to a float (the largest float <= x).
 __device__ __forceinline__ float down_f(double x) {
   float f = (float)x;
@@ -554,18 +783,60 @@ void launch_top64(const Pass64& q, const Top64& t, hipStream_t s) {
 
 void launch_dense64(const Pass64& q, const Lay64& y, hipStream_t s) {
   if (q.bt.n_rows <= 0) return;
-  // several rows per workgroup on batches that still give 4096+ workgroups,
-  // while the rows fit in 64 KB of LDS; else one (K <= 8192 always fits)
-  const int rpb = std::min(kDenseRows, (int)(64 * 1024 / (std::max(y.K, 1) * sizeof(double))));
-  if (q.bt.n_rows >= 4096 * kDenseRows && rpb == kDenseRows)
-    launch_k(dense64_rows_k, (unsigned)((q.bt.n_rows + rpb - 1) / rpb), 256, (uint32_t)(rpb * y.K * sizeof(double)),
-             s, q, y, rpb);
+  const unsigned doms = (unsigned)(q.bt.n_rows / q.bt.m);
+  // (the chords are there from kRows64 rows on: checked, since the kernel reads them)
+  const bool rows = q.chord && q.bt.n_rows >= kRows64;
+  if (rows && y.N > 256)
+    launch_k(dense64_rows_k<3, 8>, doms * ((q.bt.m + 2) / 3), 512, 0, s, q, y, y.in, y.W);
+  else if (rows)
+    launch_k(dense64_rows_k<3, 4>, doms * ((q.bt.m + 2) / 3), 256, 0, s, q, y, y.in, y.W);
   else
     launch_k(dense64_k, (unsigned)q.bt.n_rows, 256, (uint32_t)(y.K * sizeof(double)), s, q, y);
 }
 
+void launch_chord64(const float* l, const float* u, double2* ch, int64_t n, hipStream_t s) {
+  if (n > 0) launch_k(chord64_k, (unsigned)((n + 255) / 256), 256, 0, s, l, u, ch, n);
+}
+
+size_t conv64_pack_size(const ConvGeom& g) {
+  const int kc = conv64_channels(g);
+  return (size_t)g.k * g.k * g.co * ((g.ci + kc - 1) / kc * kc);
+}
+
+void launch_conv64_pack(const float* W, const ConvGeom& g, double* dst, hipStream_t s) {
+  const int kc = conv64_channels(g);
+  launch_k(conv64_pack_k, 32, 256, 0, s, W, g, (g.ci + kc - 1) / kc * kc, dst);
+}
+
 void launch_conv64(const Pass64& q, const Lay64& y, const ConvGeom& g, hipStream_t s) {
   if (q.bt.n_rows <= 0) return;
+  // (below: too few workgroups, or stride classes that fill less than a wave; a
+  // 3x32x32 network at 576 rows takes 142 us by rows of one and 124 by threes,
+  // at 288 rows 107 and 108)
+  if (y.w64 && q.chord && q.bt.n_rows >= kRows64 && g.ho > 1 && g.wo > 1 && g.hi * g.wi >= 64 * g.s * g.s) {
+    // the taps reach b0 positions before the plane and b1 after it
+    Geo64 z{};
+    int lo = 0, hi_y = g.ho - 1, hi_x = g.wo - 1;
+    for (int r = 0; r < g.s; ++r) {
+      const int i0 = (r + g.s - g.p % g.s) % g.s, taps = r < g.k ? (g.k - r + g.s - 1) / g.s : 0;
+      lo = std::min(lo, (i0 + g.p - r) / g.s - std::max(0, taps - 1));
+      hi_y = std::max(hi_y, (g.hi - 1 + g.p - r) / g.s);
+      hi_x = std::max(hi_x, (g.wi - 1 + g.p - r) / g.s);
+    }
+    z.b0 = -lo;
+    z.pw = z.b0 + hi_x + 1;
+    z.plane = z.pw * (z.b0 + hi_y + 1);
+    const int kc = conv64_channels(g);
+    z.cip = (g.ci + kc - 1) / kc * kc;
+    z.m_plane = (uint32_t)(((1ull << 32) + z.plane - 1) / z.plane);
+    z.m_pw = (uint32_t)(((1ull << 32) + z.pw - 1) / z.pw);
+    const size_t row = (size_t)g.co * z.plane * sizeof(double);
+    if (3 * row <= 64 * 1024) {
+      if (kc == 3) launch_conv64_rows<3, 3, 8>(q, y, g, z, s);
+      else launch_conv64_rows<4, 3, 8>(q, y, g, z, s);
+      return;
+    }
+  }
   const size_t row_b = (size_t)((y.K + 1) & ~1) * sizeof(double), w_b = (size_t)g.co * g.ci * g.k * g.k * sizeof(float);
   const int hw = g.hi * g.wi;
   const size_t wt_b = (size_t)g.co * g.k * g.k * (g.ci + (hw > 0 ? 256 / hw : 0) * kC64) * sizeof(float);
