@@ -47,6 +47,10 @@ inline int r32(int d) { return (d + 31) & ~31; }
 // ---------------------------------------------------------------------------
 // device memory owned by a handle
 
+// Bytes behind every device array: the dense kernels read four neighbouring
+// entries at once (gemm.hip: ld_quad), also where fewer are left.
+constexpr size_t kSlack = 64;
+
 struct DevMem {
   std::vector<void*> ptrs;
   ~DevMem() { clear(); }
@@ -59,7 +63,7 @@ struct DevMem {
     *out = nullptr;
     if (count == 0) count = 1;
     void* p = nullptr;
-    if (hipMalloc(&p, count * sizeof(T)) != hipSuccess) {
+    if (hipMalloc(&p, count * sizeof(T) + kSlack) != hipSuccess) {
       (void)hipGetLastError();
       return fail(CV_ENOMEM, "device allocation of %zu bytes failed", count * sizeof(T));
     }

@@ -39,30 +39,17 @@ __device__ __forceinline__ float4 mask4(float4 x, int row, int nrows, int k, int
   return x;
 }
 
-// Four consecutive values at p, of which the first nv exist: one 16-byte load
-// when `vec` (16-byte aligned, all four there or none), else one by one.
+// Four consecutive 32-bit values at p (4-byte aligned), in one load.  The
+// arrays it reads have room for a quad past their last entry (kSlack).
 template <class T>
-__device__ __forceinline__ void ld_quad(const T* __restrict__ p, bool vec, int nv, T (&x)[4]) {
+__device__ __forceinline__ void ld_quad(const T* __restrict__ p, T (&x)[4]) {
   static_assert(sizeof(T) == 4, "32-bit values");
-  if (vec) {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (nv > 0) v = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  typedef uint32_t quad __attribute__((ext_vector_type(4), aligned(4)));
+  const quad v = *reinterpret_cast<const quad*>(p);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = __builtin_bit_cast(T, w[r]);
-  } else {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = r < nv ? p[r] : T(0);
-  }
-}
-
-__device__ __forceinline__ void st_quad(float* p, bool vec, int nv, const float (&x)[4]) {
-  if (vec) {
-    if (nv > 0) *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
-  } else {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (r < nv) p[r] = x[r];
+  for (int r = 0; r < 4; ++r) {
+    const uint32_t w = v[r];
+    x[r] = __builtin_bit_cast(T, w);
   }
 }
 
@@ -72,11 +59,11 @@ __device__ __forceinline__ void st_quad(float* p, bool vec, int nv, const float 
 // order), so element (i, j, r) of a lane is row m0 + wm*WM + 16i + lane%16,
 // column n0 + wn*WN + 16j + 4(lane/16) + r: a lane has one row per i and four
 // neighbouring columns per j, whose status words, chords, bias and results move
-// as 16-byte pieces (`vec`: widths and offsets in whole quads), and one row's
-// indices instead of four.  The epilogue's loads and index arithmetic, not the
+// as 16-byte pieces, and one row's indices instead of four.  The epilogue's loads and index arithmetic, not the
 // MFMAs, take most of these launches: with 32x32x32 tiles 100 -> 1024 at 18432
 // rows went from 97.5 to 89.3 us, 100 -> 2048 at 9216 rows from 99.7 to 91.2,
-// 200 -> 784 with the concretisation at 9216 rows from 46.2 to 43.2.  The
+// 200 -> 784 with the concretisation at 9216 rows from 46.2 to 43.2, and, with
+// the gathers free of branches, to 81.0, 83.2 and 44.5.  The
 // adjoint keeps row 4(lane/16) + r, column lane%16: most of its traffic is the
 // packed alpha, its moments and the stored A, whose entries lie side by side
 // along a row and coalesce over the 16 lanes of one (transposed, 20 iterations
@@ -87,10 +74,12 @@ struct TileOps {
   RowInfo eri[FM][TR ? 1 : 4];
   uint32_t rec[NE];
   float2 ech[NE];
-  float ecf[NE], east[NE], ebias[FN][TR ? 4 : 1];
-  float ebe[NE];   // relaxation: beta of a split neuron (ecf holds alpha)
+  float ecf[NE];   // alpha of an unstable neuron (relaxation: or beta of a split one)
+  float ebias[FN][TR ? 4 : 1];
   float esw[NE];   // relaxation, sound mode: the neuron's rounding-error weight
+  float east[NE];  // adjoint: the stored A of an unstable neuron
   float2 emo[NE];  // adjoint with Adam: the moments of an unstable neuron's alpha
+  float ebe[NE];   // kFwdTop: C_p W(L)
 };
 
 // OCC > 0 asks the compiler for at least OCC waves per SIMD (registers capped
@@ -186,102 +175,99 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
     }
   };
 
-  // (TR) whole quads: every lane's four columns all exist or none, 16-byte aligned
-  const bool vec = MODE == kBwdConc ? (N & 3) == 0 && (bt.d0 & 3) == 0
-                                    : (N & 3) == 0 && (bt.nd & 3) == 0 && (e.layer_off & 3) == 0;
   auto row_of = [&](int i, int r) { return m0 + wm * WM + i * 16 + (TR ? csub : rsub + r); };
   auto col_of = [&](int j, int r) { return n0 + wn * WN + j * 16 + (TR ? rsub + r : csub); };
   auto elem = [&](int i, int j, int r) { return (i * FN + j) * 4 + r; };
   // (TR) columns of quad j that exist in row i of the lane
   auto count = [&](int i, int j) { return row_of(i, 0) < M ? min(max(N - col_of(j, 0), 0), 4) : 0; };
+  // the column to read for column (j, r): itself, or inside the matrix
+  auto col_in = [&](int j, int r) { return min(col_of(j, r), TR ? (N - 1) & ~3 : N - 1); };
+  // what a lane reads in place of a variable that its neuron does not have
+  const float* const none = reinterpret_cast<const float*>(bt.rbase);
 
-  // epilogue operands, first level: bias, row info and status records
+  // The gathers of the backward modes have no branch: a load under one makes
+  // every later wait count as if it had not been issued, so that waiting for
+  // the first slab would wait for the gathers of the whole tile.  Lanes without
+  // a column or a variable read some valid address.  (The adjoint's variables
+  // stay under one: five unconditional loads per entry cost it registers, 114
+  // against 92 and a wave per SIMD, 25.2 us against 22.5 at 200x200.)
+  // First level: bias, row info and status records.
   auto gather1 = [&](Ops& o) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       if constexpr (TR) {
-        if (MODE != kBwdConc) ld_quad(e.bias + col_of(j, 0), vec, min(max(N - col_of(j, 0), 0), 4), o.ebias[j]);
+        if (MODE != kBwdConc) ld_quad(e.bias + col_in(j, 0), o.ebias[j]);
       } else {
-        o.ebias[j][0] = col_of(j, 0) < N ? e.bias[col_of(j, 0)] : 0.f;
+        o.ebias[j][0] = e.bias[col_in(j, 0)];
       }
     }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      if constexpr (TR) {
-        o.eri[i][0] = row_info(bt, min(row_of(i, 0), M - 1));
+#pragma unroll
+      for (int r = 0; r < (TR ? 1 : 4); ++r) o.eri[i][r] = row_info(bt, min(row_of(i, r), M - 1));
+      if constexpr (MODE != kBwdConc) {
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          uint32_t w[4] = {kInactive, kInactive, kInactive, kInactive};
-          if (MODE != kBwdConc)
-            ld_quad(bt.status + (int64_t)o.eri[i][0].b * bt.nd + e.layer_off + col_of(j, 0), vec, count(i, j), w);
+          if constexpr (TR) {
+            uint32_t w[4];
+            ld_quad(bt.status + (int64_t)o.eri[i][0].b * bt.nd + e.layer_off + col_in(j, 0), w);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) o.rec[elem(i, j, r)] = w[r];
-        }
-      } else {
+            for (int r = 0; r < 4; ++r) o.rec[elem(i, j, r)] = w[r];
+          } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = row_of(i, r);
-          o.eri[i][r] = row_info(bt, min(row, M - 1));
-#pragma unroll
-          for (int j = 0; j < FN; ++j) {
-            const int col = col_of(j, r);
-            o.rec[elem(i, j, r)] =
-                row < M && col < N ? bt.status[(int64_t)o.eri[i][r].b * bt.nd + e.layer_off + col] : kInactive;
+            for (int r = 0; r < 4; ++r)
+              o.rec[elem(i, j, r)] = bt.status[(int64_t)o.eri[i][r].b * bt.nd + e.layer_off + col_in(j, r)];
           }
         }
       }
     }
   };
-  // second level, which needs the status records: chord and alpha / beta,
-  // the stored A for the adjoint, or the box for concretisation
+  // Second level, which needs the status records: chord and alpha / beta, the
+  // stored A for the adjoint, or the box for concretisation.
   auto gather2 = [&](Ops& o) {
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
         const int q0 = elem(i, j, 0);
+        if constexpr (MODE == kBwdConc) {
+          const int64_t pb = (int64_t)o.eri[i][0].p * bt.d0 + col_in(j, 0);
+          float lo[4], hi[4];
+          ld_quad((bt.l2x0 ? bt.l2x0 : bt.xlo) + pb, lo);
+          ld_quad((bt.l2x0 ? bt.l2x0 : bt.xhi) + pb, hi);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          o.ech[q0 + r] = make_float2(0.f, 0.f);
-          o.ecf[q0 + r] = o.east[q0 + r] = o.ebe[q0 + r] = o.esw[q0 + r] = 0.f;
-          o.emo[q0 + r] = make_float2(0.f, 0.f);
-        }
-        if constexpr (TR) {
-          const int nv = count(i, j);
+          for (int r = 0; r < 4; ++r) o.ech[q0 + r] = make_float2(lo[r], hi[r]);
+        } else if constexpr (TR) {
           const RowInfo& ri = o.eri[i][0];
-          if (MODE == kBwdConc) {
-            const int64_t pb = (int64_t)ri.p * bt.d0 + col_of(j, 0);
-            float lo[4], hi[4] = {0.f, 0.f, 0.f, 0.f};
-            ld_quad((bt.l2x0 ? bt.l2x0 : bt.xlo) + pb, vec, nv, lo);
-            if (!bt.l2x0) ld_quad(bt.xhi + pb, vec, nv, hi);
+          const int64_t pc0 = (int64_t)ri.p * bt.nd + e.layer_off + col_in(j, 0);
+          const float* const cp = reinterpret_cast<const float*>(bt.chord + pc0);  // (zero at stable neurons)
+          float c[2][4];
+          ld_quad(cp, c[0]);
+          ld_quad(cp + 4, c[1]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o.ech[q0 + r] = make_float2(lo[r], hi[r]);
-            continue;
-          }
-          const int64_t pc0 = (int64_t)ri.p * bt.nd + e.layer_off + col_of(j, 0);
-          bool any = false;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) any |= (o.rec[q0 + r] & kKindMask) == kUnstable;
-          if (any) {  // (chords are defined, zero, at stable neurons too)
-            const float* const cp = reinterpret_cast<const float*>(bt.chord + pc0);
-            float c[2][4];
-            ld_quad(cp, vec, min(2 * nv, 4), c[0]);
-            ld_quad(cp + 4, vec, max(2 * nv - 4, 0), c[1]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o.ech[q0 + r] = make_float2(c[r >> 1][2 * (r & 1)], c[r >> 1][2 * (r & 1) + 1]);
+          for (int r = 0; r < 4; ++r) {
+            o.ech[q0 + r] = make_float2(c[r >> 1][2 * (r & 1)], c[r >> 1][2 * (r & 1) + 1]);
+            if (r >= count(i, j)) o.rec[q0 + r] = kInactive;
           }
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            if (r >= nv) continue;
-            relax_vars(bt, v, ri, o.rec[q0 + r], pc0 + r, &o.ecf[q0 + r], &o.ebe[q0 + r]);
-            if (bt.sw) o.esw[q0 + r] = bt.sw[pc0 + r];
+            const uint32_t rec = o.rec[q0 + r], kind = rec & kKindMask;
+            const float* v1 = v.alpha ? v.alpha + (ri.abase + (rec & kCidxMask)) : bt.adef + (pc0 + r);
+            v1 = kind == kUnstable ? v1 : none;
+            v1 = kind == kSplit ? v.beta + ((int64_t)(rec & kSplitMask) * bt.m + ri.k) : v1;
+            o.ecf[q0 + r] = *v1;
           }
         } else {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int row = row_of(i, r), col = col_of(j, r), q = q0 + r;
             const RowInfo& ri = o.eri[i][r];
-            if (row >= M || col >= N) continue;
+            o.ech[q] = o.emo[q] = make_float2(0.f, 0.f);
+            o.east[q] = o.ecf[q] = 0.f;
+            if (row >= M || col >= N) {
+              o.rec[q] = kInactive;
+              continue;
+            }
             const int64_t pc = (int64_t)ri.p * bt.nd + e.layer_off + col;
             const bool uns = (o.rec[q] & kKindMask) == kUnstable;
             if (uns) o.ech[q] = bt.chord[pc];
@@ -292,10 +278,26 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
               if (v.adam) o.emo[q] = make_float2(v.ma[ai], v.va[ai]);
             }
             // the fused top layer: ebe holds C_p W(L) at this neuron
-            if (MODE == kFwdTop) o.ebe[q] = e.cw[ri.p * e.cw_pstride + (int64_t)ri.k * e.ldcw + col];
+            if (MODE == kFwdTop) o.ebe[q] = e.cw[ri.p * e.cw_pstride + (int64_t)ri.k * e.ldcw + col_in(j, r)];
           }
         }
       }
+    // (sound mode's float32 pass)
+    if constexpr (MODE == kBwdRelax) {
+#pragma unroll
+      for (int q = 0; q < Ops::NE; ++q) o.esw[q] = 0.f;
+      if (bt.sw) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            float w[4];
+            ld_quad(bt.sw + (int64_t)o.eri[i][0].p * bt.nd + e.layer_off + col_in(j, 0), w);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o.esw[elem(i, j, r)] = w[r];
+          }
+      }
+    }
   };
   // sum over the four lanes that share a row (lane % 16)
   auto row_sum = [&](float x) {
@@ -328,8 +330,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
             if (r >= nv) continue;
             if (MODE == kBwdRelax) {
               if (v.acomp && (o.rec[q] & kKindMask) == kUnstable) v.acomp[ri.abase + (o.rec[q] & kCidxMask)] = a;
-              x[r] = relax_value(bt, v, ri, o.rec[q], o.ech[q], relax_pick(o.rec[q], o.ecf[q], o.ebe[q]), a,
-                                 o.ebias[j][r], &cst);
+              x[r] = relax_value(bt, v, ri, o.rec[q], o.ech[q], o.ecf[q], a, o.ebias[j][r], &cst);
               cer = fmaf(fabsf(x[r]), o.esw[q], cer);
             } else if (bt.l2x0) {  // l_p ball: A(0) x0 here, - eps ||A(0)||_q in the final sum
               cst = fmaf(a, o.ech[q].x, cst);
@@ -341,8 +342,9 @@ __global__ __launch_bounds__(256, OCC) void gemm_nt(const float* __restrict__ A,
               x[r] = xstar(a > 0.f, a < 0.f, o.ech[q].x, o.ech[q].y);
             }
           }
-          if (MODE == kBwdRelax) st_quad(e.out + (int64_t)row * e.ldo + col_of(j, 0), vec, nv, x);
-          else if (v.xdense) st_quad(v.xdense + (int64_t)row * v.ldx + col_of(j, 0), vec, nv, x);
+          // (rows are padded to whole quads)
+          float* const dst = MODE == kBwdRelax ? e.out + (int64_t)row * e.ldo : v.xdense ? v.xdense + (int64_t)row * v.ldx : nullptr;
+          if (dst && nv > 0) *reinterpret_cast<float4*>(dst + col_of(j, 0)) = make_float4(x[0], x[1], x[2], x[3]);
         }
         cst = row_sum(cst);
         if (p2) cer = row_sum(cer);
