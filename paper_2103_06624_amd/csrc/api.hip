@@ -51,32 +51,89 @@ inline int r32(int d) { return (d + 31) & ~31; }
 // entries at once (gemm.hip: ld_quad), also where fewer are left.
 constexpr size_t kSlack = 64;
 
+// A handle's device arrays, dealt out of chunks (a root pass builds a handle
+// per layer: an allocation and a release for each of its 33 arrays were half of
+// its time), all released together.  Between begin() and flush() small uploads
+// gather in one staging block and reach the device in one copy.
 struct DevMem {
-  std::vector<void*> ptrs;
-  ~DevMem() { clear(); }
+  struct Chunk {
+    char* p;
+    size_t size, used;
+  };
+  static constexpr size_t kChunk = 1 << 20, kStage = 256 << 10, kAlign = 256;
+  std::vector<Chunk> chunks;
+  std::vector<char> stage;  // (host) what flush() copies to sbase
+  char* sbase = nullptr;
+  bool staging = false, keep = false;  // keep: clear() leaves the chunks for the next arrays
+  DevMem() = default;
+  DevMem(const DevMem&) = delete;
+  DevMem& operator=(const DevMem&) = delete;
+  ~DevMem() { release(); }
+  void release() {
+    for (const Chunk& c : chunks) (void)hipFree(c.p);
+    chunks.clear();
+  }
   void clear() {
-    for (void* p : ptrs) (void)hipFree(p);
-    ptrs.clear();
+    if (keep)
+      for (Chunk& c : chunks) c.used = 0;
+    else
+      release();
+    stage.clear();
+    sbase = nullptr;
+  }
+  // o's chunks, for new arrays (o's own are gone)
+  void take(DevMem& o) {
+    release();
+    chunks.swap(o.chunks);
+    for (Chunk& c : chunks) c.used = 0;
   }
   template <typename T>
   int alloc(T** out, size_t count) {
     *out = nullptr;
-    if (count == 0) count = 1;
-    void* p = nullptr;
-    if (hipMalloc(&p, count * sizeof(T) + kSlack) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(CV_ENOMEM, "device allocation of %zu bytes failed", count * sizeof(T));
+    const size_t bytes = (std::max<size_t>(count, 1) * sizeof(T) + kSlack + kAlign - 1) & ~(kAlign - 1);
+    Chunk* c = nullptr;
+    for (Chunk& q : chunks)
+      if (q.size - q.used >= bytes && (!c || q.size - q.used < c->size - c->used)) c = &q;
+    if (!c) {
+      void* p = nullptr;
+      const size_t size = std::max(bytes, kChunk);
+      if (hipMalloc(&p, size) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(CV_ENOMEM, "device allocation of %zu bytes failed", count * sizeof(T));
+      }
+      chunks.push_back(Chunk{static_cast<char*>(p), size, 0});
+      c = &chunks.back();
     }
-    ptrs.push_back(p);
-    *out = static_cast<T*>(p);
+    *out = reinterpret_cast<T*>(c->p + c->used);
+    c->used += bytes;
     return CV_OK;
   }
   template <typename T>
   int upload(T** out, const T* host, size_t count, hipStream_t s) {
-    int rc = alloc(out, count);
-    if (rc) return rc;
-    (void)s;  // blocking copy: the host buffer may be a temporary
-    if (count && host) HIPCHK(hipMemcpy(*out, host, count * sizeof(T), hipMemcpyHostToDevice));
+    (void)s;  // blocking copies: the host buffer may be a temporary
+    const size_t bytes = count * sizeof(T), room = (bytes + kSlack + kAlign - 1) & ~(kAlign - 1);
+    int rc;
+    if (staging && host && bytes && room <= kStage / 2) {
+      if (sbase && stage.size() + room > kStage && (rc = flush_stage())) return rc;
+      if (!sbase && (rc = alloc(&sbase, kStage))) return rc;
+      *out = reinterpret_cast<T*>(sbase + stage.size());
+      stage.resize(stage.size() + room);
+      std::memcpy(stage.data() + stage.size() - room, host, bytes);
+      return CV_OK;
+    }
+    if ((rc = alloc(out, count))) return rc;
+    if (count && host) HIPCHK(hipMemcpy(*out, host, bytes, hipMemcpyHostToDevice));
+    return CV_OK;
+  }
+  void begin() { staging = true; }
+  int flush() {
+    staging = false;
+    return flush_stage();
+  }
+  int flush_stage() {
+    if (sbase && !stage.empty()) HIPCHK(hipMemcpy(sbase, stage.data(), stage.size(), hipMemcpyHostToDevice));
+    stage.clear();
+    sbase = nullptr;
     return CV_OK;
   }
 };
@@ -95,6 +152,27 @@ struct DevLayer {
 };
 
 }  // namespace
+
+// A property of the code and the device, asked for once (a query is a few
+// microseconds, and every handle of a root pass makes ten of the same).
+int cvb::resident_blocks(const void* k, int threads, int smem) {
+  static std::mutex mu;
+  static std::map<std::tuple<int, const void*, int, int>, int> known;
+  int dev = 0, cus = 0, per = 0;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  std::lock_guard<std::mutex> lk(mu);
+  const auto it = known.find({dev, k, threads, smem});
+  if (it != known.end()) return it->second;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, threads, smem) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  return known[{dev, k, threads, smem}] = cus * per;
+}
 
 LaunchTiming& cvb::launch_timing() {
   thread_local LaunchTiming t;
@@ -178,6 +256,7 @@ struct cv_bound {
   uint8_t* d_defer = nullptr;  // [nd] 1 on the columns of conv layers (their split steps run after the adjoint)
   bool has_conv = false;
   int8_t* d_side = nullptr;
+  char* btab = nullptr;  // the batch's tables (Batch::prop, aoff, sptr, rbase, the splits), one block
   int forced_tiling = -1, forced_conv = -1;  // cv_bound_set_tiling / cv_bound_set_conv_variant
   int parts_req = 0;  // cv_bound_set_parts (0: two sub-batches from kPartsMinRows rows on)
   // device arrays
@@ -926,6 +1005,7 @@ void release_batch(cv_bound* h) {
   h->improved = nullptr;
   h->d_split_dom = h->d_split_col = nullptr;
   h->d_side = nullptr;
+  h->btab = nullptr;
   h->bt.prop = nullptr;
   h->bt.aoff = h->bt.rbase = h->bt.sptr = nullptr;
   h->bt.status = nullptr;
@@ -1017,6 +1097,7 @@ int set_batch(cv_bound* h, const BatchPlan& bp, bool grow, hipStream_t s) {
   h->h_aoff = aoff;
   h->n_alpha = bp.n_alpha;
   h->unst_rows_per_layer = bp.unst;
+  int rc;
   cv_bound::Cap& c = h->bcap;
   if (B > c.B || R > c.R || h->n_alpha > c.na || nnz > c.nnz || !h->bt.status) {
     HIPCHK(hipStreamSynchronize(s));
@@ -1028,41 +1109,36 @@ int set_batch(cv_bound* h, const BatchPlan& bp, bool grow, hipStream_t s) {
     c.na = sz(h->n_alpha);
     c.nnz = sz(nnz);
     DevMem& M = h->bm;
-    int rc;
-    int *d_prop;
-    int64_t *d_aoff, *d_sptr, *d_rbase;
     uint32_t* d_status;
-    if ((rc = M.alloc(&d_prop, c.B)) || (rc = M.alloc(&d_aoff, c.B + 1)) || (rc = M.alloc(&d_sptr, c.B + 1)) ||
-        (rc = M.alloc(&d_rbase, c.R)) || (rc = M.alloc(&h->d_split_dom, c.nnz)) ||
-        (rc = M.alloc(&h->d_split_col, c.nnz)) || (rc = M.alloc(&h->d_side, c.nnz)) ||
+    // the tables lie one after the other, each from a 16-byte boundary
+    if ((rc = M.alloc(&h->btab, sizeof(int) * (size_t)c.B + 2 * sizeof(int64_t) * ((size_t)c.B + 1) +
+                                    sizeof(int64_t) * (size_t)c.R + (2 * sizeof(int) + 1) * (size_t)c.nnz + 7 * 16)) ||
         (rc = M.alloc(&d_status, (size_t)c.B * nd)) || (rc = M.alloc(&h->part, (size_t)std::max<int64_t>(1, c.R) * h->n_slots)))
       return rc;
     if (n_layers >= 2 && ((rc = M.alloc(&h->act[0], (size_t)c.R * h->ldact)) ||
                           (rc = M.alloc(&h->act[1], (size_t)c.R * h->ldact))))
       return rc;
-    h->bt.prop = d_prop;
-    h->bt.aoff = d_aoff;
-    h->bt.sptr = d_sptr;
-    h->bt.rbase = d_rbase;
     h->bt.status = d_status;
   }
   std::vector<int64_t> rbase((size_t)R);
   for (int b = 0; b < B; ++b)
     for (int k = 0; k < m; ++k) rbase[(size_t)b * m + k] = aoff[b] + (int64_t)k * h->h_ucount[dom_prop[b]];
-  // blocking copies: the host arrays may be the caller's temporaries
-  auto up = [&](void* dst, const void* src, size_t bytes) -> int {
-    if (bytes) HIPCHK(hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice));
-    return CV_OK;
+  // one blocking copy: the host arrays may be the caller's temporaries
+  std::vector<char> tab;
+  auto put = [&](const void* src, size_t bytes) {
+    const size_t at = tab.size();
+    tab.resize(at + ((bytes + 15) & ~(size_t)15));
+    if (bytes) std::memcpy(tab.data() + at, src, bytes);
+    return h->btab + at;
   };
-  int rc;
-  if ((rc = up(const_cast<int*>(h->bt.prop), dom_prop, sizeof(int) * B)) ||
-      (rc = up(const_cast<int64_t*>(h->bt.aoff), aoff.data(), sizeof(int64_t) * (B + 1))) ||
-      (rc = up(const_cast<int64_t*>(h->bt.sptr), split_ptr, sizeof(int64_t) * (B + 1))) ||
-      (rc = up(const_cast<int64_t*>(h->bt.rbase), rbase.data(), sizeof(int64_t) * R)) ||
-      (rc = up(h->d_split_dom, split_dom.data(), sizeof(int) * nnz)) ||
-      (rc = up(h->d_split_col, split_col.data(), sizeof(int) * nnz)) ||
-      (rc = up(h->d_side, split_side, sizeof(int8_t) * nnz)))
-    return rc;
+  h->bt.prop = reinterpret_cast<int*>(put(dom_prop, sizeof(int) * B));
+  h->bt.aoff = reinterpret_cast<int64_t*>(put(aoff.data(), sizeof(int64_t) * (B + 1)));
+  h->bt.sptr = reinterpret_cast<int64_t*>(put(split_ptr, sizeof(int64_t) * (B + 1)));
+  h->bt.rbase = reinterpret_cast<int64_t*>(put(rbase.data(), sizeof(int64_t) * R));
+  h->d_split_dom = reinterpret_cast<int*>(put(split_dom.data(), sizeof(int) * nnz));
+  h->d_split_col = reinterpret_cast<int*>(put(split_col.data(), sizeof(int) * nnz));
+  h->d_side = reinterpret_cast<int8_t*>(put(split_side, sizeof(int8_t) * nnz));
+  HIPCHK(hipMemcpy(h->btab, tab.data(), tab.size(), hipMemcpyHostToDevice));
   uint32_t* status = const_cast<uint32_t*>(h->bt.status);
   launch_status_fill(status, h->d_kind, h->bt.prop, B, nd, s);
   launch_status_split(status, h->d_split_dom, h->d_split_col, h->d_side, nnz, nd, s);
@@ -1128,9 +1204,10 @@ int build(cv_bound* h, const cv_layer* layers, int n_layers, int P, const float*
   if ((rc = check_batch(h, B, dom_prop, split_ptr, split_layer, split_neuron, split_side, bp))) return rc;
 
   // ---- device copies of the network and of the per-property tables
+  DevMem& M = h->mem;
+  M.begin();
   rc = upload_layers(h, layers, n_layers, s);
   if (rc) return rc;
-  DevMem& M = h->mem;
   {
     std::vector<uint8_t> defer(std::max(1, nd), 0);
     for (int i = 1; i < n_layers; ++i)
@@ -1149,7 +1226,8 @@ int build(cv_bound* h, const cv_layer* layers, int n_layers, int P, const float*
       (rc = M.upload(&d_l, l, l ? (size_t)P * nd : 0, s)) || (rc = M.upload(&d_u, u, u ? (size_t)P * nd : 0, s)) ||
       (rc = M.upload(&d_xlo, x_lo, (size_t)P * h->d0, s)) || (rc = M.upload(&d_xhi, x_hi, (size_t)P * h->d0, s)) ||
       (rc = M.alloc(&d_adef, (size_t)P * nd)) || (rc = M.alloc(&d_chord, (size_t)P * nd)) ||
-      (rc = M.upload(&h->ulist, ulist.data(), ulist.size(), s)) || (rc = M.upload(&h->uoff, uoff.data(), P + 1, s)))
+      (rc = M.upload(&h->ulist, ulist.data(), ulist.size(), s)) || (rc = M.upload(&h->uoff, uoff.data(), P + 1, s)) ||
+      (rc = M.flush()))
     return rc;
   h->dl = d_l;
   h->du = d_u;
@@ -2485,6 +2563,7 @@ int root_bounds(const cv_layer* layers, int32_t n_layers, int32_t n_props, const
   std::vector<int64_t> sptr(n_props + 1, 0);
   for (int p = 0; p < n_props; ++p) prop[p] = p;
   int off = 0;
+  DevMem mem, bm;  // device memory of one sub-network after the other
   for (int i = 1; i < n_layers; ++i) {
     // sub-network of layers 1..i with specification [I; -I] on layer i
     const int d = dims[i];
@@ -2497,6 +2576,9 @@ int root_bounds(const cv_layer* layers, int32_t n_layers, int32_t n_props, const
         usub[(size_t)p * ndp + j] = up[(size_t)p * nd + j];
       }
     cv_bound hb;
+    hb.mem.take(mem);
+    hb.bm.take(bm);
+    hb.bm.keep = true;
     Spec sp;
     sp.identity = true;
     rc = build(&hb, sub.data(), i, n_props, x_lo, x_hi, 2 * d, sp, lsub.data(), usub.data(), n_props, prop.data(),
@@ -2533,6 +2615,8 @@ int root_bounds(const cv_layer* layers, int32_t n_layers, int32_t n_props, const
         up[(size_t)p * nd + off + j] = -lb[(size_t)p * 2 * d + d + j];
       }
     drop_graph(&hb);
+    mem.take(hb.mem);
+    bm.take(hb.bm);
     off += d;
   }
   for (size_t t = 0; t < lo.size(); ++t) {

@@ -1236,14 +1236,7 @@ int conv_plan_smem(const ConvPlan& pl) {
 
 int conv_plan_grid(int mode, const ConvPlan& pl) {
   const void* k = kernel_for(mode, pl.nt, pl.wg != 0);
-  int dev = 0, cus = 0, per = 0;
-  if (!k || hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, 256, pl.smem) != hipSuccess) {
-    (void)hipGetLastError();
-    return 0;
-  }
-  return cus * per;
+  return k ? std::max(0, resident_blocks(k, 256, pl.smem)) : 0;
 }
 
 int conv_plan_variant(int mode, ConvPlan& pl, int variant) {
@@ -1290,13 +1283,9 @@ void conv_plan_sd(int mode, ConvPlan& pl) {
                (mode == kBwdConc ? 0 : ((pl.dout + 3) & ~3) * (int)sizeof(float)) +
                ((pl.mpad >> 4) < kSdWaves && pl.kpad >= 32 ? kSdWaves * pl.nt * 64 * 16 : 0) +  // split-K partial tiles
                (mode == kFwdX ? 2 * std::max(0, pl.din - kSdThreads * ni) * (int)sizeof(float) : 0);  // box tail
-  int dev = 0, cus = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, kSdThreads, pl.smem_sd) != hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
-  pl.grid_sd = cus * per;
+  const int grid = resident_blocks(k, kSdThreads, pl.smem_sd);
+  if (grid < 0) return;
+  pl.grid_sd = grid;
   pl.sd = pl.grid_sd > 0 ? 1 : 0;
 }
 

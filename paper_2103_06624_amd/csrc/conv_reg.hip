@@ -780,16 +780,10 @@ void conv_plan_reg(int mode, ConvPlan& pl) {
   // (the adjoint's box in LDS, with Adam)
   const int smem = r.smem + (mode == kFwdX ? reg_box_bytes(r) : 0);
   if (smem > 64 * 1024) return;
-  int dev = 0, cus = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(reg_kernel(mode, 1, r.ntw, r.tm, r.np, r.rc)),
-                                                   64 * r.nw, smem) !=
-          hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
-  r.grid = cus * per;
+  const int grid =
+      resident_blocks(reinterpret_cast<const void*>(reg_kernel(mode, 1, r.ntw, r.tm, r.np, r.rc)), 64 * r.nw, smem);
+  if (grid < 0) return;
+  r.grid = grid;
 }
 
 int launch_conv_reg(int mode, const ConvArgs& a, hipStream_t s) {

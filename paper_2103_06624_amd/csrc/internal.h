@@ -33,6 +33,10 @@ inline void launch_k(void (*k)(P...), dim3 grid, dim3 block, uint32_t smem, hipS
   }
 }
 
+// Workgroups of kernel k (threads, dynamic LDS bytes) that fit on the current
+// device at once; -1 where the runtime cannot say.
+int resident_blocks(const void* k, int threads, int smem);
+
 // Epilogue / prologue variants of the layer kernels.
 enum Mode {
   kBwdRelax = 0,  // back-substitution, then the next ReLU layer's relaxation
