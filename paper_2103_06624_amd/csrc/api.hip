@@ -60,7 +60,9 @@ struct DevMem {
     char* p;
     size_t size, used;
   };
-  static constexpr size_t kChunk = 1 << 20, kStage = 256 << 10, kAlign = 256;
+  // arrays start 4 KiB apart (256 bytes apart, the smallest calls take 4 % longer:
+  // 23.6 us against 22.8), staged ones 256 bytes
+  static constexpr size_t kChunk = 1 << 20, kStage = 256 << 10, kAlign = 4096, kStageAlign = 256;
   std::vector<Chunk> chunks;
   std::vector<char> stage;  // (host) what flush() copies to sbase
   char* sbase = nullptr;
@@ -111,7 +113,7 @@ struct DevMem {
   template <typename T>
   int upload(T** out, const T* host, size_t count, hipStream_t s) {
     (void)s;  // blocking copies: the host buffer may be a temporary
-    const size_t bytes = count * sizeof(T), room = (bytes + kSlack + kAlign - 1) & ~(kAlign - 1);
+    const size_t bytes = count * sizeof(T), room = (bytes + kSlack + kStageAlign - 1) & ~(kStageAlign - 1);
     int rc;
     if (staging && host && bytes && room <= kStage / 2) {
       if (sbase && stage.size() + room > kStage && (rc = flush_stage())) return rc;
