@@ -602,8 +602,11 @@ def main():
         pb.set_conv_variant(args.conv_variant)
     variant_names = ["row-major/LDS weights", "row-major/global weights", "subdomain-major/LDS weights",
                      "subdomain-major/global weights"]
-    conv_plan = {f"layer{i + 1}": {"back_substitution": variant_names[pb.conv_variant(i + 1, 0)],
-                                   "adjoint": variant_names[pb.conv_variant(i + 1, 1)]}
+
+    def kernel_of(layer, direction):
+        return "register tiles" if pb.conv_tiles(layer, direction) == 1 else variant_names[pb.conv_variant(layer, direction)]
+
+    conv_plan = {f"layer{i + 1}": {"back_substitution": kernel_of(i + 1, 0), "adjoint": kernel_of(i + 1, 1)}
                  for i, ly in enumerate(wl.net.layers) if ly.kind == synth.CONV}
     a0 = pb.alpha_init()
     b0 = pb.zeros_beta()

@@ -340,22 +340,33 @@ int cv_bound_set_tiling(cv_bound *h, int32_t tiling);
  *   1  row-major, the weights read from global memory (L1/L2);
  *   2  subdomain-major: each workgroup takes the specification rows of one
  *      subdomain in turn and keeps the subdomain's status records and its
- *      property's chords (or box) in registers across them, weights in LDS
- *      (on most layers with the epilogue on the matrix cores' own tile);
+ *      property's chords (or box) in registers across them, weights in LDS;
  *   3  subdomain-major, weights from global memory.
+ * Beside them most layers have register tiles: subdomain-major, the epilogue
+ * on the matrix cores' own tile.
  * cv_bound_num_conv_variants: how many there are.
  * cv_bound_set_conv_variant: force `variant` on every conv layer of h (and of
  * its sub-batches) in both directions where it can run that layer (where it
  * cannot, the layer keeps its default), or -1 to return to the tuned choice
- * per layer shape (cv_bound_autotune's, else the default: subdomain-major
- * where an instantiation holds the layer's rows, weights in LDS up to 16 KB).
+ * per layer shape (cv_bound_autotune's, else the default: register tiles where
+ * they measured better, else subdomain-major where an instantiation holds the
+ * layer's rows, weights in LDS up to 16 KB).
  * CV_EINVAL outside -1..cv_bound_num_conv_variants()-1.
  * cv_bound_conv_variant: the variant conv layer `layer` (1..L) runs in
- * direction dir (0 back-substitution, 1 adjoint), or -1 for a dense layer or
- * bad arguments.  Host only. */
+ * direction dir (0 back-substitution, 1 adjoint; 2 on register tiles), or -1
+ * for a dense layer or bad arguments.  Host only.
+ * cv_bound_set_conv_tiles: register tiles on every conv layer that has them
+ * (1) or on none (0), whatever the variant (a first layer takes them in both
+ * directions or in neither); -1 (the start) leaves them to the variant: off
+ * where one is forced, else the tuned choice or the default.
+ * cv_bound_conv_tiles: whether that layer and direction runs on register tiles
+ * (over an l_p ball a first layer may still take the variant's kernel), or -1
+ * as above. */
 int32_t cv_bound_num_conv_variants(void);
 int cv_bound_set_conv_variant(cv_bound *h, int32_t variant);
 int cv_bound_conv_variant(const cv_bound *h, int32_t layer, int32_t dir);
+int cv_bound_set_conv_tiles(cv_bound *h, int32_t on);
+int cv_bound_conv_tiles(const cv_bound *h, int32_t layer, int32_t dir);
 
 /* Sound mode (off by default): every bound this handle reports (eval, grad,
  * upper, optimize) is rigorous: it lies below the value the same relaxation

@@ -242,6 +242,14 @@ class BoundProblem:
         """Variant conv layer `layer` (1..L) runs: direction 0 back-substitution, 1 adjoint."""
         return int(B.cv_bound_conv_variant(self.h, layer, direction))
 
+    def set_conv_tiles(self, on):
+        """Register tiles on every conv layer that has them (1), on none (0), or by variant (-1)."""
+        B.check(B.cv_bound_set_conv_tiles(self.h, on))
+
+    def conv_tiles(self, layer, direction):
+        """Whether conv layer `layer` (1..L) runs on register tiles (direction as for conv_variant)."""
+        return int(B.cv_bound_conv_tiles(self.h, layer, direction))
+
     def set_sound(self, on):
         """Lower every reported bound by a rigorous float32 rounding-error margin."""
         B.check(B.cv_bound_set_sound(self.h, int(on), _stream()))

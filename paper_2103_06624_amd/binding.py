@@ -74,6 +74,8 @@ SIGNATURES = {
     "cv_bound_num_conv_variants": (ctypes.c_int32, []),
     "cv_bound_set_conv_variant": (ctypes.c_int, [_vp, ctypes.c_int32]),
     "cv_bound_conv_variant": (ctypes.c_int, [_vp, ctypes.c_int32, ctypes.c_int32]),
+    "cv_bound_set_conv_tiles": (ctypes.c_int, [_vp, ctypes.c_int32]),
+    "cv_bound_conv_tiles": (ctypes.c_int, [_vp, ctypes.c_int32, ctypes.c_int32]),
     "cv_bound_set_sound": (ctypes.c_int, [_vp, ctypes.c_int32, _vp]),
     "cv_bound_set_input_l2": (ctypes.c_int, [_vp, _vp, _vp, _vp]),
     "cv_bound_set_input_lp": (ctypes.c_int, [_vp, _vp, _vp, ctypes.c_float, _vp]),
@@ -134,6 +136,8 @@ cv_bound_set_tiling = _fn("cv_bound_set_tiling")
 cv_bound_num_conv_variants = _fn("cv_bound_num_conv_variants")
 cv_bound_set_conv_variant = _fn("cv_bound_set_conv_variant")
 cv_bound_conv_variant = _fn("cv_bound_conv_variant")
+cv_bound_set_conv_tiles = _fn("cv_bound_set_conv_tiles")
+cv_bound_conv_tiles = _fn("cv_bound_conv_tiles")
 cv_bound_set_sound = _fn("cv_bound_set_sound")
 cv_bound_set_input_l2 = _fn("cv_bound_set_input_l2")
 cv_bound_set_input_lp = _fn("cv_bound_set_input_lp")

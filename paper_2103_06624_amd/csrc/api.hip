@@ -260,6 +260,7 @@ struct cv_bound {
   int8_t* d_side = nullptr;
   char* btab = nullptr;  // the batch's tables (Batch::prop, aoff, sptr, rbase, the splits), one block
   int forced_tiling = -1, forced_conv = -1;  // cv_bound_set_tiling / cv_bound_set_conv_variant
+  int forced_tiles = -1;                     // cv_bound_set_conv_tiles
   int parts_req = 0;  // cv_bound_set_parts (0: two sub-batches from kPartsMinRows rows on)
   // device arrays
   Batch bt{};
@@ -414,7 +415,8 @@ void couple_first(DevLayer& d) {
 
 // Kernel variant of every conv layer in both directions: `forced` >= 0 forces
 // that variant where it can run (elsewhere the default), -1 takes the tuned
-// choice for each layer shape, else the default plan.
+// choice for each layer shape, else the default plan; h->forced_tiles then puts
+// the register tiles on every layer that has them, or on none.
 void assign_conv_variants(cv_bound* h, int forced) {
   for (int i = 0; i < h->L; ++i) {
     DevLayer& d = h->layers[i];
@@ -422,7 +424,6 @@ void assign_conv_variants(cv_bound* h, int forced) {
     for (int dir = 0; dir < 2; ++dir) {
       ConvPlan& pl = dir == 0 ? d.bwd : d.fwd;
       pl = dir == 0 ? d.bwd_def : d.fwd_def;
-
       const int mode = conv_mode(i, dir == 0, false);
       int v = forced;
       if (v < 0) {
@@ -431,6 +432,7 @@ void assign_conv_variants(cv_bound* h, int forced) {
         v = it == g_conv_tune.end() ? -1 : it->second;
       }
       if (v >= 0) (void)conv_plan_variant(mode, pl, v);
+      if (h->forced_tiles >= 0) pl.reg.on = h->forced_tiles && pl.reg.grid > 0;
     }
     if (i == 0) couple_first(d);
   }
@@ -2201,8 +2203,9 @@ int set_parts(cv_bound* h, int n) {
     q->dev = h->dev;
     q->forced_tiling = h->forced_tiling;
     q->forced_conv = h->forced_conv;
+    q->forced_tiles = h->forced_tiles;
     if (h->forced_tiling >= 0) assign_tiles(q.get(), h->forced_tiling);
-    if (h->forced_conv >= 0) assign_conv_variants(q.get(), h->forced_conv);
+    if (h->forced_conv >= 0 || h->forced_tiles >= 0) assign_conv_variants(q.get(), h->forced_conv);
     q->chain_b = h->chain_b ? (q->chain_lo ? 1 : 0) : 0;
     q->chain_f = h->chain_f ? (q->chain_lo && q->chain_lo + 1 <= q->L - 1 ? 1 : 0) : 0;
     h->parts.push_back(q.release());
@@ -3227,7 +3230,9 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
   }
   // conv layers: each kernel variant timed per layer and direction on this
   // batch (the same operands as a gradient pass)
-  float first_ms[2][kNumConvVariants];
+  constexpr int kCand = kNumConvVariants + 1;  // the variants and the register tiles
+  static_assert(kConvTiles == kNumConvVariants, "the candidates are 0 .. kConvTiles");
+  float first_ms[2][kCand];
   int first_best[2] = {-1, -1};
   for (int dir = 0; dir < 2; ++dir) {
     for (int i = 1; i < L; ++i) {
@@ -3263,9 +3268,9 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
       const ConvPlan def = dir == 0 ? ly.bwd_def : ly.fwd_def;
       float best_ms = 1e30f;
       int best = -1;
-      float times[kNumConvVariants];
-      std::fill(times, times + kNumConvVariants, 1e30f);
-      for (int var = 0; var < kNumConvVariants; ++var) {
+      float times[kCand];
+      std::fill(times, times + kCand, 1e30f);
+      for (int var = 0; var < kCand; ++var) {
         ConvPlan pl = def;
         if (conv_plan_variant(mode, pl, var)) continue;
         ConvArgs a{in, h->ldact, pl, h->R, last, h->bt, v, e};
@@ -3280,14 +3285,14 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
         HIPCHK(hipEventElapsedTime(&ms, e0, e1));
         times[var] = ms;
         // (a first layer's register tiles are chosen for both directions together, below)
-        if (ms < best_ms && !(i == 1 && pl.reg.on)) {
+        if (ms < best_ms && !(i == 1 && var == kConvTiles)) {
           best_ms = ms;
           best = var;
         }
       }
       if (i == 1) {
         first_best[dir] = best;
-        std::copy(times, times + kNumConvVariants, first_ms[dir]);
+        std::copy(times, times + kCand, first_ms[dir]);
         continue;
       }
       if (best >= 0) {
@@ -3298,11 +3303,11 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
   }
   if (L >= 2 && h->layers[0].type == CV_LAYER_CONV2D) {
     // the first layer's two directions share the sign planes' order
-    const float reg = first_ms[0][2] + first_ms[1][2];
+    const float reg = first_ms[0][kConvTiles] + first_ms[1][kConvTiles];
     float old = 0.f;
     for (int dir = 0; dir < 2; ++dir) old += first_best[dir] >= 0 ? first_ms[dir][first_best[dir]] : 1e30f;
     for (int dir = 0; dir < 2; ++dir) {
-      const int v = reg < old ? 2 : first_best[dir];
+      const int v = reg < old ? kConvTiles : first_best[dir];
       std::lock_guard<std::mutex> lk(g_tune_mu);
       if (v >= 0) g_conv_tune[conv_key(conv_mode(0, dir == 0, false), h->R, h->layers[0].g)] = v;
     }
@@ -3389,6 +3394,26 @@ int cv_bound_conv_variant(const cv_bound* h, int32_t layer, int32_t dir) {
   if (d.type != CV_LAYER_CONV2D) return -1;
   const ConvPlan& pl = dir == 0 ? d.bwd : d.fwd;
   return pl.reg.on ? 2 : (pl.sd ? 2 : 0) + (pl.wg ? 1 : 0);
+}
+
+int cv_bound_set_conv_tiles(cv_bound* h, int32_t on) {
+  if (!h) return fail(CV_EINVAL, "null handle");
+  if (on < -1 || on > 1) return fail(CV_EINVAL, "conv tiles must be -1, 0 or 1");
+  std::vector<cv_bound*> all{h};
+  all.insert(all.end(), h->parts.begin(), h->parts.end());
+  for (cv_bound* q : all) {
+    q->forced_tiles = on;
+    assign_conv_variants(q, q->forced_conv);
+    drop_graph(q);
+  }
+  return CV_OK;
+}
+
+int cv_bound_conv_tiles(const cv_bound* h, int32_t layer, int32_t dir) {
+  if (!h || layer < 1 || layer > h->L || (dir != 0 && dir != 1)) return -1;
+  const DevLayer& d = h->layers[layer - 1];
+  if (d.type != CV_LAYER_CONV2D) return -1;
+  return (dir == 0 ? d.bwd : d.fwd).reg.on ? 1 : 0;
 }
 
 int cv_bound_set_tiling(cv_bound* h, int32_t tiling) {

@@ -1240,18 +1240,24 @@ int conv_plan_grid(int mode, const ConvPlan& pl) {
 }
 
 int conv_plan_variant(int mode, ConvPlan& pl, int variant) {
+  // the register tiles: the plan stays as it is built below them, for the
+  // launches that they cannot take (it fits the device: check_layers)
+  if (variant == kConvTiles) {
+    if (pl.reg.grid <= 0) return -1;
+    pl.reg.on = 1;
+    return 0;
+  }
   // 0/1: row-major kernel, 2/3: subdomain-major; odd: weights read from
   // global memory instead of LDS
   const int wg = variant & 1, sd = variant >> 1;
   ConvPlan q = pl;
+  q.reg.on = 0;
   q.wg = wg;
   q.smem = conv_plan_smem(q);
   q.grid = conv_plan_grid(mode, q);
   conv_plan_sd(mode, q);
-  const bool sd_ok = q.nj && q.smem_sd <= 65536 && q.grid_sd > 0;
-  q.reg.on = variant == 2 && q.reg.grid > 0 && (q.reg.prefer || !sd_ok);
-  if (!q.reg.on && (q.smem > 65536 || (sd && !sd_ok) || (!sd && q.grid <= 0))) return -1;
-  q.sd = sd && sd_ok;
+  if (q.smem > 65536 || (sd && (!q.nj || q.smem_sd > 65536 || q.grid_sd <= 0)) || (!sd && q.grid <= 0)) return -1;
+  q.sd = sd;
   pl = q;
   return 0;
 }

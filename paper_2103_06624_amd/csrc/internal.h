@@ -98,7 +98,7 @@ struct ConvReg {
   int np;              // K passes compiled in (0: a loop)
   int nbuf, v4;        // staged rows in LDS; whether rows are staged by float4s
   int grid, smem;
-  int prefer;          // measured better than the older kernels for such a layer
+  int prefer;          // measured better than the older kernels for such a layer: the default
   int on;              // whether launches use it
 };
 struct ConvPlan {
@@ -149,9 +149,10 @@ void conv_plan_sd(int mode, ConvPlan& pl);
 // Kernel variant of a conv plan: 0 row-major with the weights in LDS, 1
 // row-major reading them from global memory, 2 and 3 the subdomain-major
 // kernel likewise.  Rebuilds the LDS size and grids; -1 (plan unchanged)
-// when the variant cannot run this layer.
-// (2 runs the register-tile kernel of conv_reg.hip where the plan has one)
+// when the variant cannot run this layer.  kConvTiles: the register-tile kernel
+// of conv_reg.hip, over the default plan.
 constexpr int kNumConvVariants = 4;
+constexpr int kConvTiles = 4;
 // Rows of a subdomain per work unit of the subdomain-major kernels, whose
 // `grid` workgroups take the units in turn: the unit size with the fewest
 // rounds of rows, a unit's start (the subdomain's relaxation is loaded once per
