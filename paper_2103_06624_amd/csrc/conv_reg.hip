@@ -81,6 +81,12 @@ __device__ __forceinline__ float pick_bit(float a, float b, uint64_t mask) {
   return d;
 }
 
+// a b, and 0 where a or b is 0, also with the other one infinite or NaN: one
+// instruction (the intrinsic rather than asm, so that the compiler places the
+// waits for an MFMA's result)
+extern "C" __device__ float cvb_fmul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
+__device__ __forceinline__ float mul0(float a, float b) { return cvb_fmul_legacy(a, b); }
+
 // The variable code of a neuron's status word: the byte offset of an unstable
 // neuron's alpha in its row's block; a split neuron's side and index with
 // both top bits set; kNoVar otherwise.
@@ -322,13 +328,16 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
     RowInfo ri{b, r0 - b * m, p, ab0 + (int64_t)(r0 - b * m) * uc};
 
     // ---- the relaxation of the lane's neurons, for every row of the unit.
-    // Back-substitution: Lambda = a (a >= 0 ? x : c0) + sx, constant +=
-    // min(a, 0) c1, with x alpha of an unstable neuron and c0 elsewhere (1
-    // active or split z >= 0, 0 inactive or split z < 0), c0, c1 an unstable
-    // neuron's chord, sx -beta (+beta) of a split z >= 0 (z < 0) neuron.
+    // Back-substitution: Lambda = a (a >= 0 ? x : c0) + sx, constant += a c1
+    // where unstable and a < 0, with x alpha of an unstable neuron and c0
+    // elsewhere (1 active or split z >= 0, 0 inactive or split z < 0), c0, c1
+    // an unstable neuron's chord, sx -beta (+beta) of a split z >= 0 (z < 0)
+    // neuron.
     // Adjoint: zhat = x1 >= 0 ? zb x : c0 zb + c1, x1 the stored A (0 where
-    // not unstable).  Concretisation: c0, c1 the input's box.  The operations
-    // and roundings of the case analysis (common.h), the sign of a zero aside.
+    // not unstable).  Concretisation: c0, c1 the input's box.  Slopes and boxes
+    // multiply by mul0: a neuron of slope 0, and a lane without a neuron, take
+    // nothing from an a or zb that left float32.  The operations and roundings
+    // of the case analysis (common.h), the sign of a zero and 0 inf aside.
     uint32_t vo[NU];
     float c0[NU], c1[NU], x[NU], sx[NU], x1[NU], x3[NU], x4[NU];
     uint64_t any_split = 0;
@@ -529,9 +538,11 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
         for (int u = 0; u < NU; ++u) {
           const float a = acc[u / (RC * NTW)][(u / RC) % NTW][u % RC];
           // (no alpha array: x keeps the default slopes)
-          const float xp = is_unstable(vo[u]) ? x[u] : c0[u];
-          const float lam = fmaf(a, a >= 0.f ? xp : c0[u], sx[u]);
-          cst = a >= 0.f ? cst : fmaf(a, c1[u], cst);
+          const bool uns = is_unstable(vo[u]);
+          const float xp = uns ? x[u] : c0[u];
+          // (sx is 0 or the slope 0 or 1: one rounding either way)
+          const float lam = mul0(a, a >= 0.f ? xp : c0[u]) + sx[u];
+          cst = uns && !(a >= 0.f) ? fmaf(a, c1[u], cst) : cst;
           cst = fmaf(lam, kb[u], cst);
           stf(lam, ro, off(u));
           if (KIND == kMargin && bt.sw) {
@@ -545,7 +556,7 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
             const float a = acc[u / (RC * NTW)][(u / RC) % NTW][u % RC];
-            cst = fmaf(a, c0[u], cst);
+            cst = off(u) < (uint32_t)pl.dout * 4u ? fmaf(a, c0[u], cst) : cst;
             float sq = 0.f;
             const float xd = lp_entry(a, bt.lpq, &sq);
             // (a lane without a neuron: its sum of powers does not count)
@@ -558,7 +569,7 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
             const float a = acc[u / (RC * NTW)][(u / RC) % NTW][u % RC];
-            const float tm = conc_term(a, c0[u], c1[u]);
+            const float tm = fminf(mul0(a, c0[u]), mul0(a, c1[u]));
             cst += tm;
             if (KIND == kMargin) cer = fmaf(bt.sg, fabsf(tm), cer);
             if (v.xpos) {
@@ -595,7 +606,7 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
           for (int u = 0; u < NU; ++u) {
             const float zb = fmaf(rm, acc[u / (RC * NTW)][(u / RC) % NTW][u % RC], kb[u]);
             const float xp = is_unstable(vo[u]) ? x[u] : c0[u];
-            const float zh = x1[u] >= 0.f ? zb * xp : fmaf(c0[u], zb, c1[u]);
+            const float zh = x1[u] >= 0.f ? mul0(zb, xp) : fmaf(c0[u], zb, c1[u]);
             if (!last) stf(zh, ro, off(u));
             zbv[u] = zb;
           }
