@@ -16,6 +16,7 @@
 
 #include "../../include/cvbound.h"
 #include "common.h"
+#include "devmem.h"
 #include "internal.h"
 
 using namespace cvb;
@@ -24,7 +25,9 @@ namespace {
 
 thread_local std::string g_err;
 
-int fail(int code, const char* fmt, ...) {
+}  // namespace
+
+int cvb::fail(int code, const char* fmt, ...) {
   char buf[512];
   va_list ap;
   va_start(ap, fmt);
@@ -34,111 +37,14 @@ int fail(int code, const char* fmt, ...) {
   return code;
 }
 
-#define HIPCHK(expr)                                                                 \
-  do {                                                                               \
-    hipError_t e_ = (expr);                                                          \
-    if (e_ != hipSuccess) return fail(CV_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
-  } while (0)
+namespace {
 
 inline int r4(int d) { return (d + 3) & ~3; }
 inline int r16(int d) { return (d + 15) & ~15; }
 inline int r32(int d) { return (d + 31) & ~31; }
 
 // ---------------------------------------------------------------------------
-// device memory owned by a handle
-
-// Bytes behind every device array: the dense kernels read four neighbouring
-// entries at once (gemm.hip: ld_quad), also where fewer are left.
-constexpr size_t kSlack = 64;
-
-// A handle's device arrays, dealt out of chunks (a root pass builds a handle
-// per layer: an allocation and a release for each of its 33 arrays were half of
-// its time), all released together.  Between begin() and flush() small uploads
-// gather in one staging block and reach the device in one copy.
-struct DevMem {
-  struct Chunk {
-    char* p;
-    size_t size, used;
-  };
-  // arrays start 4 KiB apart (256 bytes apart, the smallest calls take 4 % longer:
-  // 23.6 us against 22.8), staged ones 256 bytes
-  static constexpr size_t kChunk = 1 << 20, kStage = 256 << 10, kAlign = 4096, kStageAlign = 256;
-  std::vector<Chunk> chunks;
-  std::vector<char> stage;  // (host) what flush() copies to sbase
-  char* sbase = nullptr;
-  bool staging = false, keep = false;  // keep: clear() leaves the chunks for the next arrays
-  DevMem() = default;
-  DevMem(const DevMem&) = delete;
-  DevMem& operator=(const DevMem&) = delete;
-  ~DevMem() { release(); }
-  void release() {
-    for (const Chunk& c : chunks) (void)hipFree(c.p);
-    chunks.clear();
-  }
-  void clear() {
-    if (keep)
-      for (Chunk& c : chunks) c.used = 0;
-    else
-      release();
-    stage.clear();
-    sbase = nullptr;
-  }
-  // o's chunks, for new arrays (o's own are gone)
-  void take(DevMem& o) {
-    release();
-    chunks.swap(o.chunks);
-    for (Chunk& c : chunks) c.used = 0;
-  }
-  template <typename T>
-  int alloc(T** out, size_t count) {
-    *out = nullptr;
-    const size_t bytes = (std::max<size_t>(count, 1) * sizeof(T) + kSlack + kAlign - 1) & ~(kAlign - 1);
-    Chunk* c = nullptr;
-    for (Chunk& q : chunks)
-      if (q.size - q.used >= bytes && (!c || q.size - q.used < c->size - c->used)) c = &q;
-    if (!c) {
-      void* p = nullptr;
-      const size_t size = std::max(bytes, kChunk);
-      if (hipMalloc(&p, size) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(CV_ENOMEM, "device allocation of %zu bytes failed", count * sizeof(T));
-      }
-      chunks.push_back(Chunk{static_cast<char*>(p), size, 0});
-      c = &chunks.back();
-    }
-    *out = reinterpret_cast<T*>(c->p + c->used);
-    c->used += bytes;
-    return CV_OK;
-  }
-  template <typename T>
-  int upload(T** out, const T* host, size_t count, hipStream_t s) {
-    (void)s;  // blocking copies: the host buffer may be a temporary
-    const size_t bytes = count * sizeof(T), room = (bytes + kSlack + kStageAlign - 1) & ~(kStageAlign - 1);
-    int rc;
-    if (staging && host && bytes && room <= kStage / 2) {
-      if (sbase && stage.size() + room > kStage && (rc = flush_stage())) return rc;
-      if (!sbase && (rc = alloc(&sbase, kStage))) return rc;
-      *out = reinterpret_cast<T*>(sbase + stage.size());
-      stage.resize(stage.size() + room);
-      std::memcpy(stage.data() + stage.size() - room, host, bytes);
-      return CV_OK;
-    }
-    if ((rc = alloc(out, count))) return rc;
-    if (count && host) HIPCHK(hipMemcpy(*out, host, bytes, hipMemcpyHostToDevice));
-    return CV_OK;
-  }
-  void begin() { staging = true; }
-  int flush() {
-    staging = false;
-    return flush_stage();
-  }
-  int flush_stage() {
-    if (sbase && !stage.empty()) HIPCHK(hipMemcpy(sbase, stage.data(), stage.size(), hipMemcpyHostToDevice));
-    stage.clear();
-    sbase = nullptr;
-    return CV_OK;
-  }
-};
+// a handle and its layers
 
 struct DevLayer {
   int type;
@@ -2584,6 +2490,8 @@ int root_bounds(const cv_layer* layers, int32_t n_layers, int32_t n_props, const
     hb.mem.take(mem);
     hb.bm.take(bm);
     hb.bm.keep = true;
+    hb.mem.peer = &hb.bm;
+    hb.bm.peer = &hb.mem;
     Spec sp;
     sp.identity = true;
     rc = build(&hb, sub.data(), i, n_props, x_lo, x_hi, 2 * d, sp, lsub.data(), usub.data(), n_props, prop.data(),
