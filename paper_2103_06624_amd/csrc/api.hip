@@ -805,7 +805,7 @@ int upload_plan(cv_bound* h, HostPlan& o, HostReg& hr, int mode, ConvPlan& out) 
     while (2 * k * (out.mpad >> 4) <= 8 && 2 * k <= (out.kpad >> 4)) k *= 2;
   }
   conv_plan_reg(mode, out);
-  out.reg.on = out.reg.grid > 0 && (out.reg.prefer || !out.sd);
+  out.reg.on = out.reg.grid > 0 && out.reg.prefer;
   return CV_OK;
 }
 
@@ -876,7 +876,7 @@ int upload_layers(cv_bound* h, const cv_layer* layers, int n, hipStream_t s) {
         // the first layer's adjoint step reads the sign planes in the order
         // the concretisation's register tiles write them
         rf.r.nwords = 0;
-        if (d.bwd.reg.on && !rf.ob.empty()) {
+        if (d.bwd.reg.grid > 0 && !rf.ob.empty()) {
           rf.xt = sign_slots(d.bwd.reg, rb.ob, pf.p);
           rf.r.nwords = rb.r.nwords;
           h->w64 = std::max(h->w64, rb.r.nwords);

@@ -127,8 +127,8 @@ constexpr int reg_occupancy() {
   return nu >= 2 ? 2 : 4;  // (eight numbers per neuron spill in 168 registers)
 }
 
-// NP > 0: the number of K passes (of 16) when compiled in (and all column tiles
-// in one wave): a lane keeps its gathers' LDS addresses in registers for every
+// NP > 0: the number of K passes (of 16) when compiled in (all column tiles in
+// one wave): a lane keeps its gathers' LDS addresses in registers for every
 // row, and a row's GEMM is LDS reads and MFMAs alone.  NP = 0: any K, the
 // column offsets in LDS too, everything read a pass ahead.
 template <int MODE, int KIND, int NTW, int TM, int NP, int RC>
@@ -693,11 +693,22 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
   }
 }
 
-// (column tiles, row tiles per wave, K passes) that are built
-#define CVB_REG_RELAX(X) X(1, 1, 0) X(1, 2, 0) X(1, 2, 6) X(2, 1, 0) X(2, 2, 0)
-#define CVB_REG_CONC(X) X(1, 1, 0) X(2, 1, 0) X(1, 2, 0) X(1, 2, 4) X(1, 4, 0) X(1, 4, 2)
-#define CVB_REG_FWDX(X) X(1, 1, 0) X(1, 1, 5) X(2, 1, 0) X(1, 2, 0) X(1, 2, 3)
-#define CVB_REG_FWD(X) X(1, 1, 0) X(2, 1, 0) X(1, 2, 0)
+// (column tiles, row tiles per wave, K passes) that are built.  The passes are
+// compiled in wherever one wave holds all column tiles and there are one to six
+// of them: the gathers' addresses take four registers a pass and row tile, and
+// with more the kernels spill (at six, 16 bytes in back-substitution with two
+// row tiles, 8 in the adjoint with Adam).  Against the loop over passes (P = 0),
+// us per launch at 9,216 rows: back-substitution 8 -> 8 k3 s1 on 16x16 64.2 and
+// 76.5, 12 -> 8 95.9 and 122.5, 4 -> 4 44.4 and 50.4; into 3x32x32 from 16
+// channels k4 s2 86.6 and 116.5, from 12 72.6 and 96.1, from 8 k3 s2 56.6 and
+// 93.6; x* into 6 channels k4 s2 77.0 and 89.2; adjoint 8 -> 6 k3 s1 68.3 and
+// 77.1.  (Concretisation takes four row tiles with one or two passes, two with
+// more: conv_plan_reg.)
+#define CVB_REG_K6(X, T) X(1, T, 0) X(1, T, 1) X(1, T, 2) X(1, T, 3) X(1, T, 4) X(1, T, 5) X(1, T, 6)
+#define CVB_REG_RELAX(X) CVB_REG_K6(X, 1) CVB_REG_K6(X, 2) X(2, 1, 0) X(2, 2, 0)
+#define CVB_REG_CONC(X) X(1, 2, 0) X(1, 2, 3) X(1, 2, 4) X(1, 2, 5) X(1, 2, 6) X(1, 4, 0) X(1, 4, 1) X(1, 4, 2) X(2, 1, 0)
+#define CVB_REG_FWDX(X) CVB_REG_K6(X, 1) CVB_REG_K6(X, 2) X(2, 1, 0)
+#define CVB_REG_FWD(X) CVB_REG_K6(X, 1) CVB_REG_K6(X, 2) X(2, 1, 0)
 
 typedef void (*reg_fn)(const float*, int, ConvPlan, int, int, Batch, Vars, Epi, int);
 
@@ -773,13 +784,25 @@ void conv_plan_reg(int mode, ConvPlan& pl) {
     break;
   }
   if (!r.nw) return;
-  // Where the older kernels remain the better ones (both measured at 73,728
-  // rows): stride-2 back-substitution with two column tiles (8 -> 8 channels
-  // k4: 403 us subdomain-major against 527 here: a third of the lanes' neurons
-  // do not exist, GEMM rows being shared by the classes), and the adjoint with
-  // eight row tiles (8 -> 8 k3 s1: 581 against 618: as many waves there, and
-  // the register tiles' eight numbers per neuron leave no room for gathers).
-  r.prefer = mode == kBwdRelax ? r.nt != 2 : mode == kFwd ? r.n_mt < 8 : 1;
+  // The default where nothing is tuned.  Register tiles win where a row is
+  // large (of 2,048 neurons and more an older kernel's thread owns four and
+  // walks them in natural order) and where its workgroups are so small that
+  // several rows run on a CU, as long as its one chain of K passes is short;
+  // in between, tiles of a row that are not whole waves' work leave the
+  // matrix cores idle.  Back-substitution through a stride-2 layer shares its
+  // GEMM rows between the classes, so that a third of a 16x16 plane's lanes have
+  // no neuron (8 -> 8 k4 s2 at 73,728 rows: 403 us subdomain-major, 527 here):
+  // it wants more neurons still.  Concretisation, which holds no variables,
+  // loses to K alone.  Over 150 networks drawn from 1 to 4 channels on 11x13 to
+  // 32x32, 1 to 3 convolutions of 3 to 32 channels, k2 to k5, s1 and s2, tiles
+  // against the variants, geometric mean over all layers and the layers they
+  // slowed by more than 3 %, at 9,216 rows: this rule 1.13 and 1 of 134
+  // (back-substitution), 1.33 and 2 of 80 (concretisation), 1.14 and none of 80
+  // (x*), 1.11 and 3 of 134 (adjoint); tiles everywhere 1.13 and 31, 1.32 and 8,
+  // 1.12 and 21, 1.11 and 31.
+  const bool small = r.nw * r.nt <= (mode == kBwdRelax ? 2 : 4) && pl.kpad <= 128;
+  const bool large = pl.dout >= 2048 && (mode != kBwdRelax || pl.dout > 2048 || (r.ts == 16 && pl.kpad >= 96));
+  r.prefer = small || large || (mode == kBwdConc && pl.kpad <= 128);
   // K passes compiled in where that kernel exists (and adds no K chunks)
   r.np = r.ksp == 1 && r.nt == r.ntw && reg_kernel(mode, 0, r.ntw, r.tm, pl.kpad >> 4, r.rc) ? pl.kpad >> 4 : 0;
   const int w = pl.kpad * r.nt * 16 * (int)sizeof(float) + (r.np ? 0 : pl.kpad * (int)sizeof(int));
