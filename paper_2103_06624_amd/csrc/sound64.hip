@@ -13,7 +13,7 @@
 // by that margin (about 1e-13 of the terms' magnitudes) plus one float ulp.
 //
 // One workgroup per batch row for the dense and convolution layers (the rows'
-// inputs in LDS), on large batches three rows of a subdomain; one wave per row
+// inputs in LDS), on large batches up to three rows of a subdomain; one wave per row
 // for the top layer.  These kernels run once per evaluation in sound
 // mode, not in the optimiser's loop.
 #include "common.h"
@@ -731,6 +731,20 @@ __global__ __launch_bounds__(64 * NW) void conv64_rows_k(Pass64 q, Lay64 y, Conv
   block_out64<kR, NW>(q, y.slot, row0, nr, cst, err, sq, red);
 }
 
+// Rows of a group: three, which every load of a weight serves, or as many as
+// leave no group partly empty where a subdomain has few.  A group computes all
+// its rows: at 3,000 rows, one a subdomain, 784-100-100 took 75 us in the
+// one-row kernel, 100 in groups of three and takes 72 in groups of one; with
+// two 131, 102 and 86 (groups of two), with four 251, 184 and 156.
+int group_rows(int m) { return m == 1 ? 1 : m == 2 || m == 4 ? 2 : 3; }
+
+template <int kR>
+void launch_dense64_rows(const Pass64& q, const Lay64& y, hipStream_t s) {
+  const unsigned groups = (unsigned)(q.bt.n_rows / q.bt.m * ((q.bt.m + kR - 1) / kR));
+  if (y.N > 256) launch_k(dense64_rows_k<kR, 8>, groups, 512, 0, s, q, y, y.in, y.W);
+  else launch_k(dense64_rows_k<kR, 4>, groups, 256, 0, s, q, y, y.in, y.W);
+}
+
 // Channels per wave item of conv64_rows_k.
 int conv64_channels(const ConvGeom& g) { return g.ci <= 3 ? 3 : 4; }
 
@@ -783,15 +797,13 @@ void launch_top64(const Pass64& q, const Top64& t, hipStream_t s) {
 
 void launch_dense64(const Pass64& q, const Lay64& y, hipStream_t s) {
   if (q.bt.n_rows <= 0) return;
-  const unsigned doms = (unsigned)(q.bt.n_rows / q.bt.m);
   // (the chords are there from kRows64 rows on: checked, since the kernel reads them)
-  const bool rows = q.chord && q.bt.n_rows >= kRows64;
-  if (rows && y.N > 256)
-    launch_k(dense64_rows_k<3, 8>, doms * ((q.bt.m + 2) / 3), 512, 0, s, q, y, y.in, y.W);
-  else if (rows)
-    launch_k(dense64_rows_k<3, 4>, doms * ((q.bt.m + 2) / 3), 256, 0, s, q, y, y.in, y.W);
-  else
-    launch_k(dense64_k, (unsigned)q.bt.n_rows, 256, (uint32_t)(y.K * sizeof(double)), s, q, y);
+  if (q.chord && q.bt.n_rows >= kRows64) {
+    const int kr = group_rows(q.bt.m);
+    kr == 1 ? launch_dense64_rows<1>(q, y, s) : kr == 2 ? launch_dense64_rows<2>(q, y, s) : launch_dense64_rows<3>(q, y, s);
+    return;
+  }
+  launch_k(dense64_k, (unsigned)q.bt.n_rows, 256, (uint32_t)(y.K * sizeof(double)), s, q, y);
 }
 
 void launch_chord64(const float* l, const float* u, double2* ch, int64_t n, hipStream_t s) {
@@ -810,10 +822,12 @@ void launch_conv64_pack(const float* W, const ConvGeom& g, double* dst, hipStrea
 
 void launch_conv64(const Pass64& q, const Lay64& y, const ConvGeom& g, hipStream_t s) {
   if (q.bt.n_rows <= 0) return;
-  // (below: too few workgroups, or stride classes that fill less than a wave; a
-  // 3x32x32 network at 576 rows takes 142 us by rows of one and 124 by threes,
-  // at 288 rows 107 and 108)
-  if (y.w64 && q.chord && q.bt.n_rows >= kRows64 && g.ho > 1 && g.wo > 1 && g.hi * g.wi >= 64 * g.s * g.s) {
+  // (below: too few workgroups, stride classes that fill less than a wave, or no
+  // second row to share a read; a 3x32x32 network at 576 rows takes 142 us by
+  // rows of one and 124 by threes, at 288 rows 107 and 108; 28x28 into 5 and 8
+  // channels with one row a subdomain, 3,000 rows, 117 by the one-row kernels,
+  // 134 by this one on single rows and 174 on groups of three)
+  if (y.w64 && q.chord && q.bt.n_rows >= kRows64 && q.bt.m > 1 && g.ho > 1 && g.wo > 1 && g.hi * g.wi >= 64 * g.s * g.s) {
     // the taps reach b0 positions before the plane and b1 after it
     Geo64 z{};
     int lo = 0, hi_y = g.ho - 1, hi_x = g.wo - 1;
@@ -832,8 +846,9 @@ void launch_conv64(const Pass64& q, const Lay64& y, const ConvGeom& g, hipStream
     z.m_pw = (uint32_t)(((1ull << 32) + z.pw - 1) / z.pw);
     const size_t row = (size_t)g.co * z.plane * sizeof(double);
     if (3 * row <= 64 * 1024) {
-      if (kc == 3) launch_conv64_rows<3, 3, 8>(q, y, g, z, s);
-      else launch_conv64_rows<4, 3, 8>(q, y, g, z, s);
+      const bool two = group_rows(q.bt.m) == 2;
+      if (kc == 3) two ? launch_conv64_rows<3, 2, 8>(q, y, g, z, s) : launch_conv64_rows<3, 3, 8>(q, y, g, z, s);
+      else two ? launch_conv64_rows<4, 2, 8>(q, y, g, z, s) : launch_conv64_rows<4, 3, 8>(q, y, g, z, s);
       return;
     }
   }
