@@ -266,16 +266,23 @@ std::mutex g_tune_mu;
 std::map<std::tuple<int, int, int, int>, int> g_tune;  // (mode, M, N, K) -> cfg
 
 // Untuned choice.  32x32 tiles keep the chip full at these skinny shapes and
-// leave room for four and more waves per SIMD.  Up to 256 columns the K loop is
-// long against the epilogue and a second K slice in flight pays (9216 rows,
-// 200x200: adjoint 21.9 us against 22.9, relaxation 18.8 against 20.1).  Above,
-// the operands of the epilogue are most of the traffic, and registers for them
-// are worth more (100 -> 512 at 73728 rows: 217 us against 234; 64x64x16 tiles,
-// two waves per SIMD, 276; 100 -> 1024 at 18432 rows: 89 against 115).
-int gemm_default_cfg(int N) {
-  if (N <= 32) return 5;    // 32x32x16
-  if (N <= 256) return 19;  // 32x32x32, two slices in flight
-  return 6;                 // 32x32x32
+// leave room for four and more waves per SIMD.  Up to 256 columns a second K
+// slice in flight pays where the K loop is long against the epilogue and the
+// rows do not fill the chip many times over (us, one slice and two: 576 rows,
+// 200x200 relaxation 6.4 and 6.1, 9,216 rows 18.0 and 17.6, but 18,432 rows 29.6
+// and 30.4; K = 100 at 9,216 rows 13.0 and 13.6; adjoint 48 -> 100 8.3 and 9.5).
+// Above, the operands of the epilogue are most of the traffic, and registers for
+// them are worth more (relaxation 100 -> 512 at 9,216 rows: 23.9, two slices
+// 25.5, 64x64x16 tiles, two waves per SIMD, 31.0).  Concretisation has the box
+// alone to read: 64x64 tiles there from two and a half per CU on (16 -> 784 at 9,216
+// rows 11.7 against 14.6 with 32x32x32, 100 -> 784 at 18,432 rows 44.8 against
+// 51.9; 200 -> 784 at 1,152 rows 11.1 against 9.9).
+int gemm_default_cfg(int mode, int M, int N, int K) {
+  if (N <= 32) return 5;  // 32x32x16
+  if (N <= 256)           // 32x32x32, two slices in flight or one
+    return K > 256 || (K > 128 && (M <= 16384 || mode == kBwdConc)) ? 19 : 6;
+  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+  return mode == kBwdConc && tiles >= 640 ? 0 : 6;  // 64x64x16, 32x32x32
 }
 
 int cfg_for(const cv_bound* h, int mode, int M, int N, int K, int fallback) {
@@ -293,9 +300,11 @@ void assign_tiles(cv_bound* h, int tiling) {
   for (int i = 1; i < n_layers; ++i) {
     if (h->layers[i - 1].type != CV_LAYER_DENSE) continue;
     const int N_b = h->dims[i - 1], K_b = h->dims[i];
-    h->cfg[i - 1] =
-        tiling >= 0 ? tiling : cfg_for(h, i - 1 >= 1 ? kBwdRelax : kBwdConc, h->R, N_b, K_b, gemm_default_cfg(N_b));
-    h->cfg[n_layers + i - 1] = tiling >= 0 ? tiling : cfg_for(h, kFwd, h->R, K_b, N_b, gemm_default_cfg(K_b));
+    auto cfg = [&](int mode, int N, int K) {
+      return tiling >= 0 ? tiling : cfg_for(h, mode, h->R, N, K, gemm_default_cfg(mode, h->R, N, K));
+    };
+    h->cfg[i - 1] = cfg(i - 1 >= 1 ? kBwdRelax : kBwdConc, N_b, K_b);
+    h->cfg[n_layers + i - 1] = cfg(kFwd, K_b, N_b);
   }
 }
 
