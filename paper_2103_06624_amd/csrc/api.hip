@@ -3147,6 +3147,8 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
   }
   // conv layers: each kernel variant timed per layer and direction on this
   // batch (the same operands as a gradient pass)
+  launch_fill(h->g_alpha, 0.5f, h->n_alpha, s);
+  launch_fill(h->adam, 0.f, 2 * h->n_alpha, s);
   constexpr int kCand = kNumConvVariants + 1;  // the variants and the register tiles
   static_assert(kConvTiles == kNumConvVariants, "the candidates are 0 .. kConvTiles");
   float first_ms[2][kCand];
@@ -3191,16 +3193,32 @@ int cv_bound_autotune(cv_bound* h, void* stream) {
         ConvPlan pl = def;
         if (conv_plan_variant(mode, pl, var)) continue;
         ConvArgs a{in, h->ldact, pl, h->R, last, h->bt, v, e};
-        auto run = [&]() { return dir == 0 ? launch_convt_bwd(mode, a, s) : launch_conv_fwd(mode, a, s); };
-        for (int w = 0; w < 2; ++w)
-          if (run()) return fail(CV_ESHAPE, "unsupported conv channels");
-        HIPCHK(hipEventRecord(e0, s));
-        for (int w = 0; w < 5; ++w) run();
-        HIPCHK(hipEventRecord(e1, s));
-        HIPCHK(hipEventSynchronize(e1));
-        float ms = 0;
-        HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-        times[var] = ms;
+        // the adjoint both as the gradient runs it and as the optimiser does,
+        // whose Adam numbers cost the kernels different shares of their waves
+        // (8 -> 8 k3 s1 at 73,728 rows, us, tiles and subdomain-major: plain 573
+        // and 567, with Adam 744 and 658)
+        times[var] = 0.f;
+        for (int ad = 0; ad <= dir; ++ad) {
+          if (ad) {
+            a.v.adam = 1;
+            a.v.bc1 = a.v.bc2 = 1.f;  // (learning rates 0: the scratch values stay)
+            a.v.alpha_w = h->g_alpha;
+            a.v.beta_w = a.v.gsplit = h->g_beta;
+            a.v.ma = a.v.mb = h->adam;
+            a.v.va = a.v.vb = h->adam + h->n_alpha;
+          }
+          auto run = [&]() { return dir == 0 ? launch_convt_bwd(mode, a, s) : launch_conv_fwd(mode, a, s); };
+          for (int w = 0; w < 2; ++w)
+            if (run()) return fail(CV_ESHAPE, "unsupported conv channels");
+          HIPCHK(hipEventRecord(e0, s));
+          for (int w = 0; w < 5; ++w) run();
+          HIPCHK(hipEventRecord(e1, s));
+          HIPCHK(hipEventSynchronize(e1));
+          float ms = 0;
+          HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+          times[var] += ms;
+        }
+        const float ms = times[var];
         // (a first layer's register tiles are chosen for both directions together, below)
         if (ms < best_ms && !(i == 1 && var == kConvTiles)) {
           best_ms = ms;
