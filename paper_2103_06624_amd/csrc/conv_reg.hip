@@ -25,14 +25,20 @@
 // kernel that spills loses to the older one.  Small workgroups (2 to 8 waves)
 // leave several rows in flight on a CU.  Measured, us per launch, older kernel
 // against this one:
-//   8 -> 8 k3 s1 back-substitution, 73,728 rows          494   409
-//   into a 3x32x32 input from 8 channels, 73,728 rows    488   406
-//   into a 3x32x32 input from 16 channels, 9,216 rows    130    85
-//   32 -> 16 k4 s2 back-substitution, 9,216 rows         312   256
-//   adjoint 8 -> 8 k4 s2, 73,728 rows                    445   365
-//   adjoint 16 -> 32 k4 s2, 9,216 rows                   259   174
-//   adjoint from x*, 3 -> 16, 9,216 rows                 187   152
-//   adjoint from x*, 3 -> 8, 73,728 rows (Adam fused)    777   802
+//   8 -> 8 k3 s1 back-substitution, 73,728 rows          475   407
+//   into a 3x32x32 input from 8 channels, 73,728 rows    483   404
+//   into a 3x32x32 input from 16 channels, 9,216 rows    129    87
+//   32 -> 16 k4 s2 back-substitution, 9,216 rows         307   259
+//   adjoint 8 -> 8 k4 s2, 73,728 rows                    443   367
+//   the same with Adam                                   461   380
+//   adjoint 16 -> 32 k4 s2, 9,216 rows                   257   170
+//   adjoint from x*, 3 -> 16, 9,216 rows                 191   137
+//   adjoint from x*, 3 -> 8, 73,728 rows                 693   653
+//   the same with Adam                                   734   718
+//   adjoint 8 -> 8 k3 s1, 73,728 rows                    567   573
+//   the same with Adam                                   658   744
+//   8 -> 8 k4 s2 back-substitution, 73,728 rows          376   614
+// (where the older kernel is the better one it is the default: conv_plan_reg).
 //
 // Lanes without a neuron (GEMM rows outside a polyphase class, padding
 // columns) are not branched round: their buffer offsets lie past the row, so
@@ -86,6 +92,14 @@ __device__ __forceinline__ float pick_bit(float a, float b, uint64_t mask) {
 // waits for an MFMA's result)
 extern "C" __device__ float cvb_fmul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
 __device__ __forceinline__ float mul0(float a, float b) { return cvb_fmul_legacy(a, b); }
+
+// The smaller of two products, the other one where one is NaN: fminf, which
+// would first pass mul0's result through an instruction of its own.
+__device__ __forceinline__ float min_num(float a, float b) {
+  float d;
+  asm("v_min_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
 
 // The variable code of a neuron's status word: the byte offset of an unstable
 // neuron's alpha in its row's block; a split neuron's side and index with
@@ -569,7 +583,8 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
             const float a = acc[u / (RC * NTW)][(u / RC) % NTW][u % RC];
-            const float tm = fminf(mul0(a, c0[u]), mul0(a, c1[u]));
+            // (0 inf of the upper edge: NaN, which the minimum leaves out)
+            const float tm = min_num(mul0(a, c0[u]), a * c1[u]);
             cst += tm;
             if (KIND == kMargin) cer = fmaf(bt.sg, fabsf(tm), cer);
             if (v.xpos) {
@@ -702,7 +717,9 @@ __global__ __launch_bounds__(64 * reg_max_waves(MODE, NTW, TM), (reg_occupancy<M
 // 76.5, 12 -> 8 95.9 and 122.5, 4 -> 4 44.4 and 50.4; into 3x32x32 from 16
 // channels k4 s2 86.6 and 116.5, from 12 72.6 and 96.1, from 8 k3 s2 56.6 and
 // 93.6; x* into 6 channels k4 s2 77.0 and 89.2; adjoint 8 -> 6 k3 s1 68.3 and
-// 77.1.  (Concretisation takes four row tiles with one or two passes, two with
+// 77.1.  Of 60 layers drawn from generic networks the loop was faster on two,
+// into 3x24x24 from 5 and 6 channels k5 s2 (47 and 56 against 54 and 62: a
+// second staged row in LDS).  (Concretisation takes four row tiles with one or two passes, two with
 // more: conv_plan_reg.)
 #define CVB_REG_K6(X, T) X(1, T, 0) X(1, T, 1) X(1, T, 2) X(1, T, 3) X(1, T, 4) X(1, T, 5) X(1, T, 6)
 #define CVB_REG_RELAX(X) CVB_REG_K6(X, 1) CVB_REG_K6(X, 2) X(2, 1, 0) X(2, 2, 0)
@@ -788,20 +805,23 @@ void conv_plan_reg(int mode, ConvPlan& pl) {
   // large (of 2,048 neurons and more an older kernel's thread owns four and
   // walks them in natural order) and where its workgroups are so small that
   // several rows run on a CU, as long as its one chain of K passes is short;
-  // in between, tiles of a row that are not whole waves' work leave the
-  // matrix cores idle.  Back-substitution through a stride-2 layer shares its
-  // GEMM rows between the classes, so that a third of a 16x16 plane's lanes have
-  // no neuron (8 -> 8 k4 s2 at 73,728 rows: 403 us subdomain-major, 527 here):
-  // it wants more neurons still.  Concretisation, which holds no variables,
-  // loses to K alone.  Over 150 networks drawn from 1 to 4 channels on 11x13 to
-  // 32x32, 1 to 3 convolutions of 3 to 32 channels, k2 to k5, s1 and s2, tiles
-  // against the variants, geometric mean over all layers and the layers they
-  // slowed by more than 3 %, at 9,216 rows: this rule 1.13 and 1 of 134
-  // (back-substitution), 1.33 and 2 of 80 (concretisation), 1.14 and none of 80
-  // (x*), 1.11 and 3 of 134 (adjoint); tiles everywhere 1.13 and 31, 1.32 and 8,
-  // 1.12 and 21, 1.11 and 31.
-  const bool small = r.nw * r.nt <= (mode == kBwdRelax ? 2 : 4) && pl.kpad <= 128;
-  const bool large = pl.dout >= 2048 && (mode != kBwdRelax || pl.dout > 2048 || (r.ts == 16 && pl.kpad >= 96));
+  // in between, tiles that a row does not fill leave the matrix cores idle.
+  // Back-substitution through a stride-2 layer shares its GEMM rows between the
+  // classes, so that a third of a 16x16 plane's lanes have no neuron (8 -> 8 k4
+  // s2 above), and the adjoint's eight numbers per neuron leave eight waves no
+  // room for more of them (8 -> 8 k3 s1 with Adam): both want more neurons
+  // still.  Concretisation, which holds no variables, loses to K alone.
+  // Over 150 networks drawn from 1 to 4 channels on 11x13 to 32x32, 1 to 3
+  // convolutions of 3 to 32 channels, k2 to k5, s1 and s2, tiles against the
+  // variants at 9,216 rows, geometric mean over all layers and the layers they
+  // slow by more than 3 %: this rule 1.10 and 1 of 134 (back-substitution), 1.33
+  // and 2 of 80 (concretisation), 1.16 and none of 80 (x*), 1.12 and 4 of 134
+  // (adjoint); tiles everywhere 1.13 and 31, 1.32 and 8, 1.12 and 21, 1.11 and
+  // 31.  At 576 rows 12 of the 428 against 87.
+  const bool small = r.nw * r.nt <= (mode == kBwdRelax ? 2 : 4) && pl.kpad <= (mode == kFwd ? 192 : 128);
+  const bool edge = mode == kBwdRelax ? r.ts == 16 && pl.kpad >= 96 : mode == kFwd ? r.nt > 1 : true;
+  const bool large = pl.dout > 2048 || (pl.dout == 2048 && edge) ||
+                     (mode == kFwdX && r.tm * r.nt == 1 && pl.dout >= 1536);
   r.prefer = small || large || (mode == kBwdConc && pl.kpad <= 128);
   // K passes compiled in where that kernel exists (and adds no K chunks)
   r.np = r.ksp == 1 && r.nt == r.ntw && reg_kernel(mode, 0, r.ntw, r.tm, pl.kpad >> 4, r.rc) ? pl.kpad >> 4 : 0;
