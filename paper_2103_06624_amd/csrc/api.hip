@@ -354,7 +354,12 @@ void assign_conv_variants(cv_bound* h, int forced) {
 }
 
 constexpr int kMaxParts = 4;             // concurrent sub-batches of the optimiser, at most
-constexpr int kPartsMinRows = 4096;      // default: two sub-batches from this many rows on
+// Default: two sub-batches from this many rows on, whose launches fill each
+// other's tails.  One and two, 20 iterations: 784-6x200-10 at 9,216 rows 6.80 and
+// 6.06 ms, at 4,608 rows 4.05 and 3.99, at 1,152 rows 2.76 and 3.11; the deep CNN
+// (3x32x32, 8 channels), whose launches have long tails no more, at 73,728 rows
+// 97.6 and 98.7, at 9,216 rows 14.5 and 15.2.
+constexpr int kPartsMinRows = 4096;
 constexpr int kChainWidth = 256;         // widest LDS-resident layer of a chain
 constexpr int kLdsBytes = 160 * 1024;    // LDS per workgroup on gfx950
 constexpr int kChainStaticLds = 64 * 32; // row-info table of the chain kernels (upper bound)
@@ -2602,7 +2607,7 @@ void free_joint(cv_bound* h) {
 // a constant summed in another order is another trajectory, so
 // back-substitution (and with it the first layer's sign planes) stays on the
 // row-order kernels; the adjoint above the first layer, whose sums over k do
-// not depend on the kernel, runs on register tiles (the K passes in one chunk,
+// not depend on the kernel, runs on its own plan (register tiles in one K chunk,
 // as in the row-major kernel that also stores zbar).
 void joint_conv_plans(cv_bound* x) {
   for (int i = 0; i < x->L; ++i) {

@@ -17,8 +17,8 @@
 // input (two with a single input buffer).
 //
 // What bounds these kernels: a row's MFMAs (192 for 8 -> 8 channels k3 s1 on a
-// 16x16 plane, 184 us of the 73,728 rows' 409), then instruction issue between
-// a row's GEMMs (about 750 VALU and 270 LDS instructions per row there, where
+// 16x16 plane, 184 us of the 73,728 rows' 407), then instruction issue between
+// a row's GEMMs (693 VALU and 240 LDS instructions per row there, where
 // the subdomain-major kernel of conv.hip, which scatters the tile through LDS
 // and walks the row in natural order between two barriers, issues 1,490 and
 // 450) and the registers, which hold the relaxation of a lane's neurons: a
@@ -845,8 +845,8 @@ int launch_conv_reg(int mode, const ConvArgs& a, hipStream_t s) {
   if (r.grid <= 0 || a.M <= 0) return -1;
   const int kind = mode >= kFwdX ? (a.v.sat ? kTrue : a.v.adam ? kAdam : kGrad)
                                  : (a.bt.sw || a.bt.l2x0 || a.e.perr || a.e.psq ? kMargin : kPlain);
-  // (a plan made for x* from sign planes may be launched over an l_p ball's
-  // dense rows, where other K passes are built: none then)
+  // (a plan made for x* from sign planes is launched as the plain adjoint over
+  // an l_p ball's dense rows)
   const reg_fn k = reg_kernel(mode, kind, r.ntw, r.tm, r.np, r.rc);
   if (!k) return -1;
   // (concretisation over an l_p ball writes no sign planes, so any kernel may

@@ -59,15 +59,17 @@ __device__ __forceinline__ void ld_quad(const T* __restrict__ p, T (&x)[4]) {
 // order), so element (i, j, r) of a lane is row m0 + wm*WM + 16i + lane%16,
 // column n0 + wn*WN + 16j + 4(lane/16) + r: a lane has one row per i and four
 // neighbouring columns per j, whose status words, chords, bias and results move
-// as 16-byte pieces, and one row's indices instead of four.  The epilogue's loads and index arithmetic, not the
-// MFMAs, take most of these launches: with 32x32x32 tiles 100 -> 1024 at 18432
-// rows went from 97.5 to 89.3 us, 100 -> 2048 at 9216 rows from 99.7 to 91.2,
-// 200 -> 784 with the concretisation at 9216 rows from 46.2 to 43.2, and, with
-// the gathers free of branches, to 81.0, 83.2 and 44.5.  The
-// adjoint keeps row 4(lane/16) + r, column lane%16: most of its traffic is the
-// packed alpha, its moments and the stored A, whose entries lie side by side
-// along a row and coalesce over the 16 lanes of one (transposed, 20 iterations
-// of 784-6x200-10 at 9216 rows take 6.31 ms instead of 6.02).
+// as 16-byte pieces, and one row's indices instead of four.  The epilogue's loads
+// and index arithmetic, not the MFMAs, take most of these launches.  Untransposed,
+// transposed, and transposed with the gathers free of branches, us with 32x32x32
+// tiles:
+//   100 -> 1024 relaxation at 18432 rows         97.5   89.3   81.0
+//   100 -> 2048 relaxation at 9216 rows          99.7   91.2   83.2
+//   200 -> 784 concretisation at 9216 rows       46.2   43.2   44.5
+// The adjoint keeps row 4(lane/16) + r, column lane%16: most of its traffic is
+// the packed alpha, its moments and the stored A, whose entries lie side by side
+// along a row and coalesce over the 16 lanes of one (transposed, 20 iterations of
+// 784-6x200-10 at 9216 rows take 6.31 ms instead of 6.02).
 template <int BM, int BN, bool TR>
 struct TileOps {
   static constexpr int FM = BM / 32, FN = BN / 32, NE = FM * FN * 4;
