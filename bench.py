@@ -183,13 +183,13 @@ def ingest_traffic(args):
         "digits) and the conv plan conv_plan_<workload> the counter runs' autotuner chose.")
     rec["_about"]["commands"] = [
         "cd /tmp && export TMPDIR=/tmp && timeout -s KILL 300 rocprofv3 --pmc FETCH_SIZE --output-format csv "
-        "-d $REPO/gpurun_out/pmc_fetch -o run -- python3 $REPO/bench.py --workload <W> --profile-only "
-        "--profile-reps 1 > $REPO/gpurun_out/pmc_fetch.out",
+        "-d $OUT/pmc_fetch -o run -- python3 $REPO/bench.py --workload <W> --profile-only "
+        "--profile-reps 1 > $OUT/pmc_fetch.out",
         "(the same with --pmc WRITE_SIZE into pmc_write)",
-        "timeout -s KILL 120 rocprofv3 --pmc FETCH_SIZE --output-format csv -d $REPO/gpurun_out/cal_fetch -o run "
+        "timeout -s KILL 120 rocprofv3 --pmc FETCH_SIZE --output-format csv -d $OUT/cal_fetch -o run "
         "-- python3 $REPO/bench.py --calib-only --calib-copy-mib 256 (and WRITE_SIZE into cal_write)",
-        "python3 bench.py --ingest-traffic gpurun_out/pmc_fetch gpurun_out/pmc_write gpurun_out/cal_fetch "
-        "gpurun_out/cal_write gpurun_out/pmc_fetch.out"]
+        "python3 bench.py --ingest-traffic $OUT/pmc_fetch $OUT/pmc_write $OUT/cal_fetch "
+        "$OUT/cal_write $OUT/pmc_fetch.out"]
     rec["_about"][f"factors_{prof['workload']}"] = {"fetch": round(ff, 4), "write": round(fw, 4)}
     rec["_about"][f"conv_plan_{prof['workload']}"] = prof["conv_plan"]
     rec[prof["workload"]] = ent
